@@ -17,7 +17,11 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfx.so")
-SOURCES = ["fx.cpp", "tables.cpp", "batch.cpp", "kernels.hip", "kernels_p2.hip", "kernels_ct.hip", "kernels_cfp.hip", "pair.hip", "farfield.hip", "brute.hip", "noalloc.hip"]
+SOURCES = ["fx.cpp", "tables.cpp", "batch.cpp", "kernels.hip", "kernels_p2.hip", "kernels_ct.hip", "kernels_cfp.hip", "kernels_fold.hip", "pair.hip", "farfield.hip", "brute.hip", "noalloc.hip"]
+
+# Per-source flags. kernels_fold.hip: its kernels switch between many butterflies inside the loop over the
+# terms; hoisting the FP64 constants of all of them out of that loop costs hundreds of scalar-register spills.
+EXTRA_FLAGS = {"kernels_fold.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def hipcc() -> str:
@@ -38,7 +42,7 @@ def build(verbose: bool = True, arch: str = "gfx950") -> str:
 
     def compile_one(src):
         obj = os.path.join(objdir, src + ".o")
-        cmd = common + ["-c", "-o", obj, os.path.join(CSRC, src)]
+        cmd = common + EXTRA_FLAGS.get(src, []) + ["-c", "-o", obj, os.path.join(CSRC, src)]
         res = subprocess.run(cmd, capture_output=True, text=True)
         return src, obj, cmd, res
 

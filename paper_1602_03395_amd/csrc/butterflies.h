@@ -1,0 +1,205 @@
+// Register butterflies of any composite or prime radix used by the folded line kernels: v <- DFT_R(v),
+// sign - (forward) or + (INV), unnormalised, everything unrolled at compile time.
+//
+// Primes from 5 on pair v[k] with v[R - k] (cosines on the sums, sines on the differences: half the
+// products of the direct sum); coprime factors use the prime-factor index map, which needs no
+// twiddles; 8, 9, 16 and 25 split into two equal or near-equal factors with constant twiddles.
+#pragma once
+
+#include "device_common.h"
+
+namespace fx {
+
+// cos(2 pi k / N), sin(2 pi k / N)
+constexpr double kCos3[3] = {
+    1.0, -0.5, -0.5};
+constexpr double kSin3[3] = {
+    0.0, 0.8660254037844386, -0.8660254037844386};
+constexpr double kCos5[5] = {
+    1.0, 0.30901699437494745, -0.8090169943749475, -0.8090169943749475, 0.30901699437494745};
+constexpr double kSin5[5] = {
+    0.0, 0.9510565162951535, 0.5877852522924731, -0.5877852522924731, -0.9510565162951535};
+constexpr double kCos7[7] = {
+    1.0, 0.6234898018587335, -0.2225209339563144, -0.9009688679024191, -0.9009688679024191,
+    -0.2225209339563144, 0.6234898018587335};
+constexpr double kSin7[7] = {
+    0.0, 0.7818314824680298, 0.9749279121818236, 0.4338837391175581, -0.4338837391175581, -0.9749279121818236,
+    -0.7818314824680298};
+constexpr double kCos9[9] = {
+    1.0, 0.766044443118978, 0.17364817766693036, -0.5, -0.9396926207859084, -0.9396926207859084, -0.5,
+    0.17364817766693036, 0.766044443118978};
+constexpr double kSin9[9] = {
+    0.0, 0.6427876096865394, 0.984807753012208, 0.8660254037844386, 0.3420201433256687, -0.3420201433256687,
+    -0.8660254037844386, -0.984807753012208, -0.6427876096865394};
+constexpr double kCos11[11] = {
+    1.0, 0.8412535328311812, 0.41541501300188644, -0.14231483827328514, -0.6548607339452851,
+    -0.9594929736144974, -0.9594929736144974, -0.6548607339452851, -0.14231483827328514, 0.41541501300188644,
+    0.8412535328311812};
+constexpr double kSin11[11] = {
+    0.0, 0.5406408174555976, 0.9096319953545183, 0.9898214418809327, 0.7557495743542583, 0.28173255684142967,
+    -0.28173255684142967, -0.7557495743542583, -0.9898214418809327, -0.9096319953545183, -0.5406408174555976};
+constexpr double kCos13[13] = {
+    1.0, 0.8854560256532099, 0.5680647467311558, 0.12053668025532305, -0.3546048870425356, -0.7485107481711011,
+    -0.970941817426052, -0.970941817426052, -0.7485107481711011, -0.3546048870425356, 0.12053668025532305,
+    0.5680647467311558, 0.8854560256532099};
+constexpr double kSin13[13] = {
+    0.0, 0.46472317204376856, 0.8229838658936564, 0.992708874098054, 0.9350162426854148, 0.6631226582407952,
+    0.23931566428755777, -0.23931566428755777, -0.6631226582407952, -0.9350162426854148, -0.992708874098054,
+    -0.8229838658936564, -0.46472317204376856};
+constexpr double kCos16[16] = {
+    1.0, 0.9238795325112867, 0.7071067811865476, 0.3826834323650898, 0.0, -0.3826834323650898,
+    -0.7071067811865476, -0.9238795325112867, -1.0, -0.9238795325112867, -0.7071067811865476,
+    -0.3826834323650898, 0.0, 0.3826834323650898, 0.7071067811865476, 0.9238795325112867};
+constexpr double kSin16[16] = {
+    0.0, 0.3826834323650898, 0.7071067811865476, 0.9238795325112867, 1.0, 0.9238795325112867,
+    0.7071067811865476, 0.3826834323650898, 0.0, -0.3826834323650898, -0.7071067811865476, -0.9238795325112867,
+    -1.0, -0.9238795325112867, -0.7071067811865476, -0.3826834323650898};
+constexpr double kCos25[25] = {
+    1.0, 0.9685831611286311, 0.8763066800438636, 0.7289686274214116, 0.5358267949789967, 0.30901699437494745,
+    0.06279051952931337, -0.18738131458572463, -0.42577929156507266, -0.6374239897486897, -0.8090169943749475,
+    -0.9297764858882515, -0.9921147013144779, -0.9921147013144779, -0.9297764858882515, -0.8090169943749475,
+    -0.6374239897486897, -0.42577929156507266, -0.18738131458572463, 0.06279051952931337, 0.30901699437494745,
+    0.5358267949789967, 0.7289686274214116, 0.8763066800438636, 0.9685831611286311};
+constexpr double kSin25[25] = {
+    0.0, 0.2486898871648548, 0.48175367410171527, 0.6845471059286887, 0.8443279255020151, 0.9510565162951535,
+    0.9980267284282716, 0.9822872507286887, 0.9048270524660196, 0.7705132427757893, 0.5877852522924731,
+    0.368124552684678, 0.12533323356430426, -0.12533323356430426, -0.368124552684678, -0.5877852522924731,
+    -0.7705132427757893, -0.9048270524660196, -0.9822872507286887, -0.9980267284282716, -0.9510565162951535,
+    -0.8443279255020151, -0.6845471059286887, -0.48175367410171527, -0.2486898871648548};
+
+template <int N> __host__ __device__ constexpr double root_cos(int k) {
+    if constexpr (N == 3) return kCos3[k];
+    else if constexpr (N == 5) return kCos5[k];
+    else if constexpr (N == 7) return kCos7[k];
+    else if constexpr (N == 9) return kCos9[k];
+    else if constexpr (N == 11) return kCos11[k];
+    else if constexpr (N == 13) return kCos13[k];
+    else if constexpr (N == 16) return kCos16[k];
+    else return kCos25[k];
+}
+template <int N> __host__ __device__ constexpr double root_sin(int k) {
+    if constexpr (N == 3) return kSin3[k];
+    else if constexpr (N == 5) return kSin5[k];
+    else if constexpr (N == 7) return kSin7[k];
+    else if constexpr (N == 9) return kSin9[k];
+    else if constexpr (N == 11) return kSin11[k];
+    else if constexpr (N == 13) return kSin13[k];
+    else if constexpr (N == 16) return kSin16[k];
+    else return kSin25[k];
+}
+
+// a times exp(-+ 2 pi i K / N)
+template <typename T, int N, bool INV> __device__ __forceinline__ C<T> cmul_root(C<T> a, double co, double si) {
+    const T c = (T)co, s = INV ? (T)si : (T)-si;
+    return mk<T>(a.x * c - a.y * s, a.x * s + a.y * c);
+}
+
+__host__ __device__ constexpr int fold_factor(int R) {
+    // first factor A of R = A B; 1 for primes
+    switch (R) {
+        case 4: return 2;
+        case 6: return 2;
+        case 8: return 4;
+        case 9: return 3;
+        case 10: return 2;
+        case 12: return 4;
+        case 14: return 2;
+        case 15: return 3;
+        case 16: return 4;
+        case 18: return 2;
+        case 20: return 4;
+        case 24: return 8;
+        case 25: return 5;
+        default: return 1;
+    }
+}
+__host__ __device__ constexpr int fold_gcd(int a, int b) { return b == 0 ? a : fold_gcd(b, a % b); }
+// the multiple of B that is 1 mod A (A, B coprime): x = (i unit(A, B) + j unit(B, A)) mod A B has
+// x = i mod A and x = j mod B
+__host__ __device__ constexpr int fold_unit(int A, int B) {
+    int x = 0;
+    while (x % A != 1 % A) x += B;
+    return x;
+}
+
+template <typename T, int R, bool INV> __device__ __forceinline__ void bfly(C<T>* v) {
+    if constexpr (R == 1) {
+    } else if constexpr (R == 2 || R == 3 || R == 4 || R == 8) {
+        Bfly<T, R>::run(v, INV);
+    } else if constexpr (fold_factor(R) == 1) {
+        constexpr int H = (R - 1) / 2;
+        C<T> s[H], d[H];
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            s[k] = cadd<T>(v[k + 1], v[R - 1 - k]);
+            d[k] = csub<T>(v[k + 1], v[R - 1 - k]);
+        }
+        const C<T> v0 = v[0];
+#pragma unroll
+        for (int k = 0; k < H; ++k) v[0] = cadd<T>(v[0], s[k]);
+#pragma unroll
+        for (int u = 1; u <= H; ++u) {
+            C<T> a = v0, b = mk<T>(0, 0);
+#pragma unroll
+            for (int k = 1; k <= H; ++k) {
+                const T c = (T)root_cos<R>((u * k) % R), z = (T)root_sin<R>((u * k) % R);
+                a.x += c * s[k - 1].x;
+                a.y += c * s[k - 1].y;
+                b.x += z * d[k - 1].x;
+                b.y += z * d[k - 1].y;
+            }
+            // forward: a - i b at u, a + i b at R - u
+            const C<T> ib = mk<T>(-b.y, b.x);
+            v[INV ? u : R - u] = cadd<T>(a, ib);
+            v[INV ? R - u : u] = csub<T>(a, ib);
+        }
+    } else {
+        constexpr int A = fold_factor(R), B = R / A;
+        C<T> y[R];  // [n2][k1] after the A-point transforms
+        if constexpr (fold_gcd(A, B) == 1) {
+            constexpr int eA = fold_unit(A, B), eB = fold_unit(B, A);
+#pragma unroll
+            for (int n2 = 0; n2 < B; ++n2) {
+                C<T> w[A];
+#pragma unroll
+                for (int n1 = 0; n1 < A; ++n1) w[n1] = v[(B * n1 + A * n2) % R];
+                bfly<T, A, INV>(w);
+#pragma unroll
+                for (int k1 = 0; k1 < A; ++k1) y[n2 * A + k1] = w[k1];
+            }
+#pragma unroll
+            for (int k1 = 0; k1 < A; ++k1) {
+                C<T> w[B];
+#pragma unroll
+                for (int n2 = 0; n2 < B; ++n2) w[n2] = y[n2 * A + k1];
+                bfly<T, B, INV>(w);
+#pragma unroll
+                for (int k2 = 0; k2 < B; ++k2) v[(k1 * eA + k2 * eB) % R] = w[k2];
+            }
+        } else {
+#pragma unroll
+            for (int n2 = 0; n2 < B; ++n2) {
+                C<T> w[A];
+#pragma unroll
+                for (int n1 = 0; n1 < A; ++n1) w[n1] = v[B * n1 + n2];
+                bfly<T, A, INV>(w);
+#pragma unroll
+                for (int k1 = 0; k1 < A; ++k1) {
+                    if (n2 == 0 || k1 == 0) y[n2 * A + k1] = w[k1];
+                    else y[n2 * A + k1] = cmul_root<T, R, INV>(w[k1], root_cos<R>(n2 * k1), root_sin<R>(n2 * k1));
+                }
+            }
+#pragma unroll
+            for (int k1 = 0; k1 < A; ++k1) {
+                C<T> w[B];
+#pragma unroll
+                for (int n2 = 0; n2 < B; ++n2) w[n2] = y[n2 * A + k1];
+                bfly<T, B, INV>(w);
+#pragma unroll
+                for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = w[k2];
+            }
+        }
+    }
+}
+
+}  // namespace fx

@@ -26,6 +26,28 @@ struct RadixPlan {
 
 RadixPlan make_radix_plan(int n);
 
+// Plan of the folded line kernels (kernels_fold.hip): the stages of the length-P transforms, the last
+// one fused with the product with HT and the first inverse stage; the inverse runs them backwards.
+constexpr int kFoldStages = 12;
+struct FoldDiv {
+    int d = 1;
+    float inv = 1.f, half = 0.5f;  // 1 / d and 1 / (2 d)
+};
+struct FoldStage {
+    int R = 1;
+    FoldDiv nb, m;   // P / R butterflies; m = P / (R and the radices before): distance of their inputs
+    int mp = 1, Lp = 1;  // that distance and the block length R m with the padding
+    int tw = 0;      // first entry of the stage's twiddles
+};
+struct FoldPlan {
+    int n = 0, M = 1, P = 1, g = 1;
+    int cls = 0;     // radix class (the kernels are built per class)
+    int pad = 0;     // one element of padding after every Rl (the last radix) of a slot
+    int ntw = 0;     // twiddles of all stages
+    FoldDiv dM, dP, dg, d1, dRl;
+    FoldStage st[kFoldStages];
+};
+
 // Per-axis device view of the method's tables, for data type T (float or double).
 // Table layout: [lam][M] complex, row q.
 //   TA[q][n]  = exp(-i alpha_q (x_n - a))                         (presA premultiply)
@@ -41,6 +63,9 @@ struct AxisDev {
     const void* HTx = nullptr; // HT arranged for the select-free first reduction step (or null)
     const void* HTl = nullptr; // [lam][g][P] (each lane's P values contiguous): for power-of-two
                                // P <= min(g, 8) row n2 turned by bitrev(n2 mod P), else HTx reordered
+    const void* FT = nullptr;  // table of the folded line kernels (or null)
+    const FoldPlan* fold = nullptr;   // plan of those kernels (or null): host copy
+    const FoldPlan* foldd = nullptr;  // and device copy
     int M = 1;        // axis length
     int P = 1;        // M / g: number of distinct n'' values (output-pruned length)
     int g = 1;        // gcd(lam, M)
@@ -70,6 +95,16 @@ struct PassGeom {
     bool erw = false;    // E pass (g = 8, P = 16..64, contiguous lines): register form, a line per 8 P / V lanes
     bool erg = false;    // E, EA or EH pass (g = 2, 4, 8; P = 16..64): register form, a line per g P / 8 lanes
     bool eh2 = false;    // EH pass: compile-time power-of-two kernel, one output line per workgroup
+    // E, EA or EH pass by the folded line kernels: 2^flts lines and fqr terms per step, fqpw terms per
+    // workgroup (E), fgs groups of subsequences summed side by side, input read from global memory
+    // instead of an LDS copy (fdirect); LDS strides of a slot, a row and a raw line. For contiguous
+    // lines Qin and A count every line as one row of lines; fA is the original A.
+    bool fold = false;
+    bool fdirect = false;
+    int flts = 0, fqr = 1, fqpw = 1, fgs = 1, fps = 1, frs = 1, fraw = 1;
+    int64_t fA = 1;
+    double fcycles = 0;  // predicted duration
+    FoldDiv dgs;
 };
 
 enum class Kind { E, A, EA, EH, AH, EAH, AA, AAH };
@@ -121,6 +156,7 @@ struct AxisTables {
     std::vector<double> HT;              // [lam][P][g] when requested, else empty
     std::vector<double> HTx;             // HT for odd n2 lanes swapped or sign-modulated (see build_ht)
     std::vector<double> HTl;             // [lam][g][P], rows turned for the rotated reduction (see build_ht)
+    std::vector<double> FT;              // rows and stage twiddles of the folded line kernels (see build_ft)
 };
 struct AxisParams {
     int64_t M = 1;
@@ -130,7 +166,8 @@ struct AxisParams {
     // Optional spectrum: phase[i] = t * omega(kappa_l) in radians for the fine wave
     // number l = i - floor(lam M / 2); NULL keeps hbar t kappa^2 / 2m.
     const double* phase = nullptr;
-    bool want_ht = false;  // also build the chirp-folded table HT
+    bool want_ht = false;  // also build the chirp-folded table HT in its register-kernel layouts
+    const FoldPlan* fold = nullptr;  // also build the rows of the folded line kernels for this plan
 };
 AxisTables build_axis_tables(const AxisParams& p);
 
@@ -196,6 +233,13 @@ hipError_t launch_pass_ehr(bool dbl, const void* in, void* out, const AxisDev& a
 bool asr_applicable(int g, int max_g);
 hipError_t launch_pass_asr(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
                            int accumulate, void* rho, hipStream_t st);
+
+// Folded line kernels (kernels_fold.hip): E, EA and EH for any pruned length with prime factors up to 13.
+bool make_fold_plan(FoldPlan& pl, int M, int g);
+bool fold_geometry(Kind kind, bool dbl, const FoldPlan& pl, PassGeom& g, int cus);
+size_t fold_lds_bytes(Kind kind, bool dbl, const FoldPlan& pl, const PassGeom& g);
+hipError_t launch_pass_fold(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
+                            int accumulate, void* rho, hipStream_t st);
 
 void set_error(const std::string& msg);
 

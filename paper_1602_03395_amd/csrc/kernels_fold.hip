@@ -1,0 +1,917 @@
+// Folded line kernels: E, EA and EH for any pruned length P = M / g whose prime factors are at most 13
+// (fold_device.h has the method and the LDS layout).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <functional>
+#include <mutex>
+#include <numeric>
+#include <set>
+#include <vector>
+
+#include "fold_device.h"
+#include "fx_internal.h"
+
+namespace fx {
+
+namespace {
+
+// Where the lines of a workgroup's tile live in the input and output tensors.
+struct FoldTile {
+    int64_t in0;    // element offset of line 0, point 0 in a tensor of M-point lines
+    int64_t lead;   // strided: slice * A + a of the tile; contiguous: first line
+    int64_t s0;     // first column of a strided tile
+    int nl;         // lines present
+};
+
+// Element offset of line l, point 0, in a tensor of M-point lines.
+__device__ __forceinline__ int64_t fold_line(const FoldPlan& pl, const PassGeom& g, const FoldTile& tl, int l) {
+    return g.S == 1 ? tl.in0 + (int64_t)l * pl.M : tl.in0 + l;
+}
+
+// Element offset of line l, sample 0, of term i (counted from g.qb) in the tensor [..][qn][A][P][S]
+// that E writes and EH reads.
+__device__ __forceinline__ int64_t fold_pruned(const FoldPlan& pl, const PassGeom& g, const FoldTile& tl, int l,
+                                               int i) {
+    if (g.S == 1) {
+        const int64_t line = tl.lead + l;
+        if (g.fA == g.A) return (i * g.A + line) * pl.P;  // one input slice
+        const int64_t qi = (unsigned)line / (unsigned)g.fA;
+        return ((qi * g.qn + i) * g.fA + (line - qi * g.fA)) * pl.P;
+    }
+    const int64_t qi = tl.lead / g.A;
+    return (((qi * g.qn + i) * g.A + (tl.lead - qi * g.A)) * pl.P) * g.S + tl.s0 + l;
+}
+
+// Table entry `i` (the table is under 4 GiB: a 32-bit byte offset from a uniform base).
+template <typename T> __device__ __forceinline__ const C<T>* fold_tab(const C<T>* tab, int q, int wtab, int i) {
+    const unsigned off = ((unsigned)q * (unsigned)wtab + (unsigned)i) * (unsigned)sizeof(C<T>);
+    return (const C<T>*)((const char*)tab + off);
+}
+
+template <typename T> struct FoldArgs {
+    const C<T>* in;
+    const C<T>* tab;   // table rows
+    const C<T>* tw;    // stage twiddles in LDS
+    C<T>* X;           // row buffers
+    const C<T>* raw;   // the tile's input in LDS, or null (read from global memory)
+    int nrow, ntq;     // rows of a full step, terms present in this one
+    int q0;            // first term of this step (absolute)
+};
+
+// First forward stage: the input of every row times TA.
+template <typename T> struct FoldFirst {
+    const FoldArgs<T>& a;
+    const FoldPlan& pl;
+    const PassGeom& g;
+    const FoldTile& tl;
+    template <int R> __device__ __forceinline__ void run() {
+        const FoldStage& st = pl.st[0];
+        const int m = st.m.d, mp = st.mp, lf = g.S == 1 ? 0 : g.flts;
+        const int total = a.nrow * pl.g * m;
+        const int wtab = (pl.g + 2) * pl.P;
+        const C<T>* w = a.tw + st.tw;
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+            const FoldItem it = fold_item(idx, lf, st.nb, pl.dg);
+            const int l = it.row & ((1 << g.flts) - 1), k = it.jj;
+            const int q = a.q0 + min(it.row >> g.flts, a.ntq - 1);
+            const C<T>* ta = fold_tab<T>(a.tab, q, wtab, pl.M + k);
+            C<T> v[R];
+            if (a.raw) {
+                const C<T>* x = a.raw + __mul24(l, g.fraw) + it.n2 * pl.P + k;
+#pragma unroll
+                for (int t = 0; t < R; ++t) v[t] = cmul<T>(x[t * m], ta[t * m]);
+            } else {
+                const int64_t S = g.S;
+                const C<T>* x = a.in + fold_line(pl, g, tl, min(l, tl.nl - 1)) + (int64_t)(pl.g * k + it.n2) * S;
+                const int64_t step = (int64_t)pl.g * m * S;
+#pragma unroll
+                for (int t = 0; t < R; ++t) v[t] = x[t * step];
+#pragma unroll
+                for (int t = 0; t < R; ++t) v[t] = cmul<T>(v[t], ta[t * m]);
+            }
+            bfly<T, R, false>(v);
+#pragma unroll
+            for (int t = 1; t < R; ++t) v[t] = cmul<T>(v[t], w[(t - 1) * m + k]);
+            C<T>* y = a.X + __mul24(it.row, g.frs) + __mul24(it.n2, g.fps) + k + (pl.pad ? fdivu(k, pl.dRl) : 0);
+#pragma unroll
+            for (int t = 0; t < R; ++t) y[t * mp] = v[t];
+        }
+    }
+};
+
+// What becomes of the samples E_q[u], u = u0 + t us, of one row.
+template <typename T, bool EA> struct FoldSink {
+    C<T>* out;          // E: global output; EA: the accumulators H in LDS
+    const FoldTile& tl;
+    const PassGeom& g;
+    const FoldPlan& pl;
+    const C<T>* tab;
+    int q0, ntq;
+    template <int R> __device__ __forceinline__ void put(const C<T>* v, int row, int u0, int us) const {
+        const int l = row & ((1 << g.flts) - 1), qr = row >> g.flts;
+        if (l >= tl.nl || qr >= ntq) return;
+        const int i = q0 + qr - g.qb;
+        if constexpr (!EA) {
+            C<T>* o = out + fold_pruned(pl, g, tl, l, i) + u0 * g.S;
+            const int64_t step = us * g.S;
+#pragma unroll
+            for (int t = 0; t < R; ++t) o[t * step] = v[t];
+        } else {
+            const int j = i - fdivu(i, pl.dg) * pl.g;
+            const C<T>* tf = fold_tab<T>(tab, q0 + qr, (pl.g + 2) * pl.P, pl.M + pl.P + u0);
+            C<T>* h = out + __mul24(l, g.fraw) + j * pl.P + u0;
+#pragma unroll
+            for (int t = 0; t < R; ++t) h[t * us] = cfma<T>(h[t * us], tf[t * us], v[t]);
+        }
+    }
+};
+
+// Last forward stage, product with HT and sum over the subsequences (of one group); with a single
+// group also the first inverse stage.
+template <typename T, bool EA> struct FoldFused {
+    const FoldArgs<T>& a;
+    const FoldPlan& pl;
+    const PassGeom& g;
+    const FoldTile& tl;
+    const FoldSink<T, EA>& sink;
+    template <int R> __device__ __forceinline__ void run() {
+        const FoldStage& st = pl.st[pl.n - 1];
+        const int nb = st.nb.d, lf = g.S == 1 ? 0 : g.flts;
+        const int total = a.nrow * nb * g.fgs;
+        const int wtab = (pl.g + 2) * pl.P;
+        const bool one = pl.n == 1;
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+            const FoldItem it = fold_item(idx, lf, st.nb, g.dgs);
+            const int l = it.row & ((1 << g.flts) - 1);
+            const int q = a.q0 + min(it.row >> g.flts, a.ntq - 1);
+            const C<T>* ht = fold_tab<T>(a.tab, q, wtab, it.jj * R);
+            C<T>* row = a.X + __mul24(it.row, g.frs) + it.jj * (R + pl.pad);
+            C<T> acc[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) acc[t] = mk<T>(0, 0);
+            for (int n2 = it.n2; n2 < pl.g; n2 += g.fgs) {
+                C<T> v[R];
+                if (!one) {
+                    const C<T>* x = row + __mul24(n2, g.fps);
+#pragma unroll
+                    for (int t = 0; t < R; ++t) v[t] = x[t];
+                } else {
+                    const C<T>* ta = fold_tab<T>(a.tab, q, wtab, pl.M);
+                    if (a.raw) {
+                        const C<T>* x = a.raw + __mul24(l, g.fraw) + n2 * pl.P;
+#pragma unroll
+                        for (int t = 0; t < R; ++t) v[t] = cmul<T>(x[t], ta[t]);
+                    } else {
+                        const int64_t S = g.S;
+                        const C<T>* x = a.in + fold_line(pl, g, tl, min(l, tl.nl - 1)) + (int64_t)n2 * S;
+                        const int64_t step = (int64_t)pl.g * S;
+#pragma unroll
+                        for (int t = 0; t < R; ++t) v[t] = cmul<T>(x[t * step], ta[t]);
+                    }
+                }
+                bfly<T, R, false>(v);
+                const C<T>* h = ht + n2 * pl.P;
+#pragma unroll
+                for (int t = 0; t < R; ++t) acc[t] = cfma<T>(acc[t], h[t], v[t]);
+            }
+            if (g.fgs > 1) {
+#pragma unroll
+                for (int t = 0; t < R; ++t) row[__mul24(it.n2, g.fps) + t] = acc[t];
+                continue;
+            }
+            bfly<T, R, true>(acc);
+            if (one) {
+                sink.template put<R>(acc, it.row, 0, 1);
+            } else {
+#pragma unroll
+                for (int t = 0; t < R; ++t) row[t] = acc[t];
+            }
+        }
+    }
+};
+
+// The groups' sums added up, and the first inverse stage.
+template <typename T, bool EA> struct FoldJoin {
+    const FoldArgs<T>& a;
+    const FoldPlan& pl;
+    const PassGeom& g;
+    const FoldSink<T, EA>& sink;
+    template <int R> __device__ __forceinline__ void run() {
+        const FoldStage& st = pl.st[pl.n - 1];
+        const int lf = g.S == 1 ? 0 : g.flts;
+        const int total = a.nrow * st.nb.d;
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+            const FoldItem it = fold_item(idx, lf, st.nb, pl.d1);
+            C<T>* row = a.X + __mul24(it.row, g.frs) + it.jj * (R + pl.pad);
+            C<T> acc[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) acc[t] = row[t];
+            for (int j = 1; j < g.fgs; ++j) {
+#pragma unroll
+                for (int t = 0; t < R; ++t) acc[t] = cadd<T>(acc[t], row[j * g.fps + t]);
+            }
+            bfly<T, R, true>(acc);
+            if (pl.n == 1) {
+                sink.template put<R>(acc, it.row, 0, 1);
+            } else {
+#pragma unroll
+                for (int t = 0; t < R; ++t) row[t] = acc[t];
+            }
+        }
+    }
+};
+
+// Last inverse stage, its outputs given to the sink.
+template <typename T, bool EA> struct FoldLast {
+    const FoldArgs<T>& a;
+    const FoldPlan& pl;
+    const PassGeom& g;
+    const FoldSink<T, EA>& sink;
+    template <int R> __device__ __forceinline__ void run() {
+        const FoldStage& st = pl.st[0];
+        const int m = st.m.d, mp = st.mp, lf = g.S == 1 ? 0 : g.flts;
+        const int total = a.nrow * m;
+        const C<T>* w = a.tw + st.tw;
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+            const FoldItem it = fold_item(idx, lf, st.nb, pl.d1);
+            const int k = it.jj;
+            const C<T>* x = a.X + __mul24(it.row, g.frs) + k + (pl.pad ? fdivu(k, pl.dRl) : 0);
+            C<T> v[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) v[t] = x[t * mp];
+#pragma unroll
+            for (int t = 1; t < R; ++t) v[t] = cmulc<T>(v[t], w[(t - 1) * m + k]);
+            bfly<T, R, true>(v);
+            sink.template put<R>(v, it.row, k, m);
+        }
+    }
+};
+
+// Tile of a workgroup: workgroups of one XCD take a contiguous range of tiles, the chunks of terms of
+// a tile next to each other, so that neighbouring tiles and all terms of a tile share one L2.
+__device__ __forceinline__ bool fold_decode(const PassGeom& g, int nchunk, int& tile, int& chunk) {
+    const int per = (int)((g.Qin * g.ntiles + 7) >> 3);
+    const int x = blockIdx.x & 7, y = blockIdx.x >> 3;
+    const int tl = (unsigned)y / (unsigned)nchunk;
+    chunk = y - tl * nchunk;
+    tile = x * per + tl;
+    return tile < (int)(g.Qin * g.ntiles);
+}
+
+__device__ __forceinline__ FoldTile fold_tile(const FoldPlan& pl, const PassGeom& g, int tile) {
+    const int qi = (unsigned)tile / (unsigned)g.ntiles;
+    const Tile t = decode_tile(g, tile - qi * (int)g.ntiles);
+    FoldTile r;
+    r.nl = t.nl;
+    r.s0 = t.s0;
+    r.lead = qi * g.A + t.a0;
+    r.in0 = r.lead * pl.M * g.S + t.s0;
+    return r;
+}
+
+// Copies the input of the tile into LDS, subsequence by subsequence; missing lines read as the last one.
+template <typename T>
+__device__ void fold_load(const C<T>* __restrict__ in, C<T>* __restrict__ raw, const PassGeom& g, const FoldPlan& pl,
+                          const FoldTile& tl) {
+    const int M = pl.M, TS = 1 << g.flts, total = M << g.flts;
+    for (int e0 = threadIdx.x; e0 < total; e0 += 4 * blockDim.x) {
+        C<T> v[4];
+        int d[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int e = e0 + k * (int)blockDim.x;
+            d[k] = -1;
+            v[k] = mk<T>(0, 0);
+            if (e < total) {
+                int l, n;
+                if (g.S == 1) {
+                    l = fdivu(e, pl.dM);
+                    n = e - l * M;
+                } else {
+                    l = e & (TS - 1);
+                    n = e >> g.flts;
+                }
+                const int n1 = fdivu(n, pl.dg);
+                d[k] = __mul24(l, g.fraw) + (n - n1 * pl.g) * pl.P + n1;
+                v[k] = in[fold_line(pl, g, tl, min(l, tl.nl - 1)) + (int64_t)n * g.S];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (d[k] >= 0) raw[d[k]] = v[k];
+    }
+}
+
+// The rows of one step through every stage. Each stage starts with a barrier.
+template <typename T, int RC, bool EA>
+__device__ __forceinline__ void fold_rows(const FoldArgs<T>& a, const FoldPlan& pl, const PassGeom& g,
+                                          const FoldTile& tl, C<T>* out) {
+    const int lf = g.S == 1 ? 0 : g.flts;
+    const FoldSink<T, EA> sink{out, tl, g, pl, a.tab, a.q0, a.ntq};
+    if (pl.n > 1) {
+        FoldFirst<T> first{a, pl, g, tl};
+        fold_radix<RC, false>(pl.st[0].R, first);
+        for (int s = 1; s + 1 < pl.n; ++s) {
+            FoldMid<T, false> mid{a.X, a.tw, pl.st[s], pl, a.nrow * pl.g * pl.st[s].nb.d, lf, pl.dg, g.frs, g.fps};
+            fold_radix<RC, false>(pl.st[s].R, mid);
+        }
+    }
+    FoldFused<T, EA> fu{a, pl, g, tl, sink};
+    fold_radix<RC, true>(pl.st[pl.n - 1].R, fu);
+    if (g.fgs > 1) {
+        FoldJoin<T, EA> jo{a, pl, g, sink};
+        fold_radix<RC, true>(pl.st[pl.n - 1].R, jo);
+    }
+    if (pl.n > 1) {
+        for (int s = pl.n - 2; s > 0; --s) {
+            FoldMid<T, true> mid{a.X, a.tw, pl.st[s], pl, a.nrow * pl.st[s].nb.d, lf, pl.d1, g.frs, g.fps};
+            fold_radix<RC, false>(pl.st[s].R, mid);
+        }
+        FoldLast<T, EA> last{a, pl, g, sink};
+        fold_radix<RC, false>(pl.st[0].R, last);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void fold_copy(C<T>* dst, const C<T>* __restrict__ src, int n) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
+}
+
+// Waves per SIMD that a kernel's registers are bound to. Only the FP64 E of class 1 gains from a bound
+// (1080-point lines, one term: 148 -> 127 us); elsewhere the scheduling for fewer registers costs
+// more than the extra waves bring (375 points, class 3: 56 -> 72 us).
+__host__ __device__ constexpr int fold_bound(bool dbl, int cls, bool e) { return dbl && cls == 1 && e ? 3 : 1; }
+
+// ------------------------------------------------------------------------------------
+// E: in [Qin][A][M][S] -> out [Qin * qn][A][P][S]
+// ------------------------------------------------------------------------------------
+template <typename T, int RC>
+__global__ __launch_bounds__(kThreads, fold_bound(sizeof(T) == 8, RC, true)) void k_EF(const C<T>* __restrict__ in, C<T>* __restrict__ out,
+                                                 const C<T>* __restrict__ tab, const C<T>* __restrict__ twg,
+                                                 const FoldPlan* __restrict__ plp, PassGeom g) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const FoldPlan& pl = *plp;
+    const int nchunk = (g.qn + g.fqpw - 1) / g.fqpw;
+    int tile, chunk;
+    if (!fold_decode(g, nchunk, tile, chunk)) return;
+    const FoldTile tl = fold_tile(pl, g, tile);
+    C<T>* tw = (C<T>*)smem;
+    C<T>* X = tw + pl.ntw;
+    C<T>* raw = X + (g.fqr << g.flts) * g.frs;
+    fold_copy<T>(tw, twg, pl.ntw);
+    if (!g.fdirect) fold_load<T>(in, raw, g, pl, tl);
+    const int i0 = chunk * g.fqpw, i1 = min(g.qn, i0 + g.fqpw);
+    for (int i = i0; i < i1; i += g.fqr) {
+        const int ntq = min(g.fqr, i1 - i);
+        const FoldArgs<T> a{in, tab, tw, X, g.fdirect ? nullptr : raw, g.fqr << g.flts, ntq, g.qb + i};
+        fold_rows<T, RC, false>(a, pl, g, tl, out);
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// EA: every term of a line in one workgroup. The sums over the terms of equal residue j = i mod g
+// of the term index build up in LDS, H[line][j][u]; the g-point inverse transform over j follows
+// once per tile (Tf_q[n0 + P c] = Tf_q[n0] exp(2 pi i q c / g)).
+// in [Qin][A][M][S] -> out [Qin][A][M][S]
+// ------------------------------------------------------------------------------------
+template <typename T, int RC>
+__global__ __launch_bounds__(kThreads, fold_bound(sizeof(T) == 8, RC, false)) void k_EAF(const C<T>* __restrict__ in, C<T>* __restrict__ out,
+                                                  const C<T>* __restrict__ tab, const C<T>* __restrict__ twg,
+                                                  const C<T>* __restrict__ roots, const FoldPlan* __restrict__ plp,
+                                                  PassGeom g, int lg, int accumulate, T* __restrict__ rho) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const FoldPlan& pl = *plp;
+    int tile, chunk;
+    if (!fold_decode(g, 1, tile, chunk)) return;
+    const FoldTile tl = fold_tile(pl, g, tile);
+    const int M = pl.M, P = pl.P, G = pl.g, TS = 1 << g.flts;
+    C<T>* H = (C<T>*)smem;
+    C<T>* rg = H + TS * g.fraw;  // exp(-2 pi i k / g)
+    C<T>* tw = rg + G;
+    C<T>* X = tw + pl.ntw;
+    C<T>* raw = X + (g.fqr << g.flts) * g.frs;
+    fold_copy<T>(tw, twg, pl.ntw);
+    for (int e = threadIdx.x; e < G; e += blockDim.x) rg[e] = roots[(int64_t)e * P];
+    for (int e = threadIdx.x; e < TS * g.fraw; e += blockDim.x) H[e] = mk<T>(0, 0);
+    if (!g.fdirect) fold_load<T>(in, raw, g, pl, tl);
+    for (int i = 0; i < g.qn; i += g.fqr) {
+        const int ntq = min(g.fqr, g.qn - i);
+        const FoldArgs<T> a{in, tab, tw, X, g.fdirect ? nullptr : raw, g.fqr << g.flts, ntq, g.qb + i};
+        fold_rows<T, RC, true>(a, pl, g, tl, H);
+    }
+    __syncthreads();
+    const int total = M << g.flts;
+    for (int e = threadIdx.x; e < total; e += blockDim.x) {
+        int l, nb;
+        if (g.S == 1) {
+            l = fdivu(e, pl.dM);
+            nb = e - l * M;
+        } else {
+            l = e & (TS - 1);
+            nb = e >> g.flts;
+        }
+        if (l >= tl.nl) continue;
+        const int c = fdivu(nb, pl.dP);
+        const int n0 = nb - c * P;
+        const int u = (unsigned)(n0 * lg) % (unsigned)P;
+        const C<T>* h = H + __mul24(l, g.fraw) + u;
+        C<T> v;
+        if (G == 1) {
+            v = h[0];
+        } else {
+            int k = (int)(((int64_t)g.qb * c) % G);
+            v = mk<T>(0, 0);
+            for (int j = 0; j < G; ++j) {
+                v = cfmac<T>(v, h[j * P], rg[k]);
+                k += c;
+                if (k >= G) k -= G;
+            }
+        }
+        const int64_t o = fold_line(pl, g, tl, l) + (int64_t)nb * g.S;
+        if (accumulate) v = cadd<T>(v, out[o]);
+        out[o] = v;
+        if (rho) rho[o] = v.x * v.x + v.y * v.y;
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// EH: adjoint of E, summed over the terms: in [Qo * qn][A][P][S] -> out [Qo][A][M][S],
+//   out[g . + n2] = sum_q conj(TA_q) IDFT_P( conj(HT_q[n2]) DFT_P(in_q) ).
+// With several groups of subsequences the forward transform sits in a slot of its own (slot g), so
+// that every group can read it while others write; with one group it sits in slot 0.
+// ------------------------------------------------------------------------------------
+template <typename T> struct FoldAdj {
+    const C<T>* in;
+    const C<T>* tab;
+    const C<T>* tw;
+    C<T>* X;
+    C<T>* acc;         // sums of the tile, or null: the rows keep their results
+    const FoldPlan& pl;
+    const PassGeom& g;
+    const FoldTile& tl;
+    int nrow, ntq, i0;  // i0: first term of this step, counted from g.qb
+    __device__ __forceinline__ int src() const { return g.fgs > 1 ? pl.g * g.fps : 0; }
+    __device__ __forceinline__ const C<T>* input(int row) const {
+        const int l = min(row & ((1 << g.flts) - 1), tl.nl - 1), qr = min(row >> g.flts, ntq - 1);
+        return in + fold_pruned(pl, g, tl, l, i0 + qr);
+    }
+};
+
+template <typename T> struct FoldAdjFirst {  // first forward stage, read from global memory
+    const FoldAdj<T>& a;
+    template <int R> __device__ __forceinline__ void run() {
+        const FoldPlan& pl = a.pl;
+        const PassGeom& g = a.g;
+        const FoldStage& st = pl.st[0];
+        const int m = st.m.d, mp = st.mp, lf = g.S == 1 ? 0 : g.flts;
+        const int total = a.nrow * m;
+        const C<T>* w = a.tw + st.tw;
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+            const FoldItem it = fold_item(idx, lf, st.nb, pl.d1);
+            const int k = it.jj;
+            const C<T>* x = a.input(it.row) + k * g.S;
+            const int64_t step = m * g.S;
+            C<T> v[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) v[t] = x[t * step];
+            bfly<T, R, false>(v);
+#pragma unroll
+            for (int t = 1; t < R; ++t) v[t] = cmul<T>(v[t], w[(t - 1) * m + k]);
+            C<T>* y = a.X + __mul24(it.row, g.frs) + a.src() + k + (pl.pad ? fdivu(k, pl.dRl) : 0);
+#pragma unroll
+            for (int t = 0; t < R; ++t) y[t * mp] = v[t];
+        }
+    }
+};
+
+// Last forward stage, product with conj(HT) and first inverse stage of every subsequence.
+template <typename T> struct FoldAdjFused {
+    const FoldAdj<T>& a;
+    template <int R> __device__ __forceinline__ void run() {
+        const FoldPlan& pl = a.pl;
+        const PassGeom& g = a.g;
+        const FoldStage& st = pl.st[pl.n - 1];
+        const int lf = g.S == 1 ? 0 : g.flts;
+        const int total = a.nrow * st.nb.d * g.fgs;
+        const int wtab = (pl.g + 2) * pl.P;
+        const bool one = pl.n == 1;
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+            const FoldItem it = fold_item(idx, lf, st.nb, g.dgs);
+            const int qr = min(it.row >> g.flts, a.ntq - 1);
+            const C<T>* ht = fold_tab<T>(a.tab, g.qb + a.i0 + qr, wtab, it.jj * R);
+            C<T>* row = a.X + __mul24(it.row, g.frs) + it.jj * (R + pl.pad);
+            C<T> v[R];
+            if (!one) {
+                const C<T>* x = row + a.src();
+#pragma unroll
+                for (int t = 0; t < R; ++t) v[t] = x[t];
+            } else {
+                const C<T>* x = a.input(it.row);
+#pragma unroll
+                for (int t = 0; t < R; ++t) v[t] = x[t * g.S];
+            }
+            bfly<T, R, false>(v);
+            const C<T>* ta = ht + pl.M;
+            for (int n2 = it.n2; n2 < pl.g; n2 += g.fgs) {
+                const C<T>* h = ht + n2 * pl.P;
+                C<T> w[R];
+#pragma unroll
+                for (int t = 0; t < R; ++t) w[t] = cmulc<T>(v[t], h[t]);
+                bfly<T, R, true>(w);
+                C<T>* y = row + __mul24(n2, g.fps);
+                if (one) {
+#pragma unroll
+                    for (int t = 0; t < R; ++t) y[t] = cmulc<T>(w[t], ta[t]);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < R; ++t) y[t] = w[t];
+                }
+            }
+        }
+    }
+};
+
+// Last inverse stage of every subsequence, times conj(TA): left in the row, or (one term at a time)
+// added to the tile's sums.
+template <typename T> struct FoldAdjLast {
+    const FoldAdj<T>& a;
+    template <int R> __device__ __forceinline__ void run() {
+        const FoldPlan& pl = a.pl;
+        const PassGeom& g = a.g;
+        const FoldStage& st = pl.st[0];
+        const int m = st.m.d, mp = st.mp, lf = g.S == 1 ? 0 : g.flts;
+        const int total = a.nrow * pl.g * m;
+        const int wtab = (pl.g + 2) * pl.P;
+        const C<T>* w = a.tw + st.tw;
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+            const FoldItem it = fold_item(idx, lf, st.nb, pl.dg);
+            const int qr = min(it.row >> g.flts, a.ntq - 1), k = it.jj;
+            const C<T>* ta = fold_tab<T>(a.tab, g.qb + a.i0 + qr, wtab, pl.M + k);
+            C<T>* x = a.X + __mul24(it.row, g.frs) + __mul24(it.n2, g.fps) + k + (pl.pad ? fdivu(k, pl.dRl) : 0);
+            C<T> v[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) v[t] = x[t * mp];
+#pragma unroll
+            for (int t = 1; t < R; ++t) v[t] = cmulc<T>(v[t], w[(t - 1) * m + k]);
+            bfly<T, R, true>(v);
+            if (a.acc) {
+                C<T>* s = a.acc + __mul24(it.row, g.fraw) + it.n2 * pl.P + k;
+#pragma unroll
+                for (int t = 0; t < R; ++t) s[t * m] = cfmac<T>(s[t * m], v[t], ta[t * m]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < R; ++t) x[t * mp] = cmulc<T>(v[t], ta[t * m]);
+            }
+        }
+    }
+};
+
+template <typename T, int RC>
+__global__ __launch_bounds__(kThreads, fold_bound(sizeof(T) == 8, RC, false)) void k_EHF(const C<T>* __restrict__ in, C<T>* __restrict__ out,
+                                                  const C<T>* __restrict__ tab, const C<T>* __restrict__ twg,
+                                                  const FoldPlan* __restrict__ plp, PassGeom g, int accumulate) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const FoldPlan& pl = *plp;
+    int tile, chunk;
+    if (!fold_decode(g, 1, tile, chunk)) return;
+    const FoldTile tl = fold_tile(pl, g, tile);
+    const int M = pl.M, P = pl.P, TS = 1 << g.flts, nrow = g.fqr << g.flts;
+    const int lf = g.S == 1 ? 0 : g.flts;
+    C<T>* acc = (C<T>*)smem;
+    C<T>* tw = acc + TS * g.fraw;
+    C<T>* X = tw + pl.ntw;
+    fold_copy<T>(tw, twg, pl.ntw);
+    for (int e = threadIdx.x; e < TS * g.fraw; e += blockDim.x) acc[e] = mk<T>(0, 0);
+    const bool direct = pl.n > 1 && g.fqr == 1;
+    for (int i = 0; i < g.qn; i += g.fqr) {
+        const int ntq = min(g.fqr, g.qn - i);
+        const FoldAdj<T> a{in, tab, tw, X, direct ? acc : nullptr, pl, g, tl, nrow, ntq, i};
+        if (pl.n > 1) {
+            FoldAdjFirst<T> first{a};
+            fold_radix<RC, false>(pl.st[0].R, first);
+            for (int s = 1; s + 1 < pl.n; ++s) {
+                FoldMid<T, false> mid{X + a.src(), tw, pl.st[s], pl, nrow * pl.st[s].nb.d, lf, pl.d1, g.frs, g.fps};
+                fold_radix<RC, false>(pl.st[s].R, mid);
+            }
+        }
+        FoldAdjFused<T> fu{a};
+        fold_radix<RC, true>(pl.st[pl.n - 1].R, fu);
+        if (pl.n > 1) {
+            for (int s = pl.n - 2; s > 0; --s) {
+                FoldMid<T, true> mid{X, tw, pl.st[s], pl, nrow * pl.g * pl.st[s].nb.d, lf, pl.dg, g.frs, g.fps};
+                fold_radix<RC, false>(pl.st[s].R, mid);
+            }
+            FoldAdjLast<T> last{a};
+            fold_radix<RC, false>(pl.st[0].R, last);
+        }
+        if (!direct) {  // the rows of one line added up
+            __syncthreads();
+            for (int e = threadIdx.x; e < TS * M; e += blockDim.x) {
+                const int l = fdivu(e, pl.dM);
+                const int at = e - l * M;
+                const int n2 = fdivu(at, pl.dP);
+                const int n1 = at - n2 * P;
+                const C<T>* x = X + __mul24(l, g.frs) + __mul24(n2, g.fps) + n1 + (pl.pad ? fdivu(n1, pl.dRl) : 0);
+                C<T> v = acc[__mul24(l, g.fraw) + at];
+                for (int r = 0; r < ntq; ++r) v = cadd<T>(v, x[r * TS * g.frs]);
+                acc[__mul24(l, g.fraw) + at] = v;
+            }
+        }
+    }
+    __syncthreads();
+    const int total = M << g.flts;
+    for (int e = threadIdx.x; e < total; e += blockDim.x) {
+        int l, at;
+        if (g.S == 1) {
+            l = fdivu(e, pl.dM);
+            at = e - l * M;
+        } else {
+            l = e & (TS - 1);
+            at = e >> g.flts;
+        }
+        if (l >= tl.nl) continue;
+        const int n1 = fdivu(at, pl.dg);
+        C<T> v = acc[__mul24(l, g.fraw) + (at - n1 * pl.g) * P + n1];
+        const int64_t o = fold_line(pl, g, tl, l) + (int64_t)at * g.S;
+        if (accumulate) v = cadd<T>(v, out[o]);
+        out[o] = v;
+    }
+}
+
+template <typename K> hipError_t prep_lds_fold(K kernel, size_t bytes) {
+    if (bytes <= 65536) return hipSuccess;
+    static std::mutex mu;
+    static std::set<const void*> done;
+    std::lock_guard<std::mutex> lk(mu);
+    if (done.count((const void*)kernel)) return hipSuccess;
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       lds_limit_bytes());
+    if (e == hipSuccess) done.insert((const void*)kernel);
+    return e;
+}
+
+template <typename T, int RC>
+hipError_t launch_fold_T(Kind kind, const void* in, void* out, const AxisDev& ax, const PassGeom& g, int accumulate,
+                         void* rho, hipStream_t st) {
+    const size_t lds = fold_lds_bytes(kind, sizeof(T) == 8, *ax.fold, g);
+    const C<T>* tab = (const C<T>*)ax.FT;
+    const C<T>* tw = tab + (int64_t)ax.lam * (ax.g + 2) * ax.P;
+    const int64_t per = (g.Qin * g.ntiles + 7) / 8;
+    hipError_t e = hipSuccess;
+    if (kind == Kind::E) {
+        const int64_t nchunk = (g.qn + g.fqpw - 1) / g.fqpw;
+        if (8 * per * nchunk >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+        auto k = k_EF<T, RC>;
+        if ((e = prep_lds_fold(k, lds)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k, dim3((unsigned)(8 * per * nchunk)), dim3(kThreads), lds, st, (const C<T>*)in,
+                           (C<T>*)out, tab, tw, ax.foldd, g);
+    } else if (kind == Kind::EA) {
+        auto k = k_EAF<T, RC>;
+        if ((e = prep_lds_fold(k, lds)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k, dim3((unsigned)(8 * per)), dim3(kThreads), lds, st, (const C<T>*)in, (C<T>*)out, tab,
+                           tw, (const C<T>*)ax.tw, ax.foldd, g, ax.lg, accumulate, (T*)rho);
+    } else if (kind == Kind::EH) {
+        auto k = k_EHF<T, RC>;
+        if ((e = prep_lds_fold(k, lds)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k, dim3((unsigned)(8 * per)), dim3(kThreads), lds, st, (const C<T>*)in, (C<T>*)out, tab,
+                           tw, ax.foldd, g, accumulate);
+    } else {
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+FoldDiv fold_div(int d) {
+    FoldDiv r;
+    r.d = d;
+    r.inv = 1.0f / (float)d;
+    r.half = 0.5f / (float)d;
+    return r;
+}
+
+// Factors of P out of `radices`, as few as possible; among those the smallest sum.
+// Ascending on return, the first at most `fused`; empty when there are none.
+std::vector<int> fold_factors(int P, const std::vector<int>& radices, int fused) {
+    std::vector<int> best, cur;
+    std::function<void(int, size_t)> rec = [&](int m, size_t lo) {
+        if (m == 1) {
+            if (cur.front() > fused) return;
+            const int a = std::accumulate(cur.begin(), cur.end(), 0), b = std::accumulate(best.begin(), best.end(), 0);
+            if (best.empty() || cur.size() < best.size() || (cur.size() == best.size() && a < b)) best = cur;
+            return;
+        }
+        if (!best.empty() && cur.size() + 1 > best.size()) return;
+        for (size_t i = lo; i < radices.size(); ++i) {
+            if (m % radices[i]) continue;
+            cur.push_back(radices[i]);
+            rec(m / radices[i], i);
+            cur.pop_back();
+        }
+    };
+    if (P == 1) return {1};
+    rec(P, 0);
+    return best;
+}
+
+}  // namespace
+
+bool make_fold_plan(FoldPlan& pl, int M, int g) {
+    if (g < 1 || M % g) return false;
+    pl = FoldPlan();
+    pl.M = M;
+    pl.g = g;
+    pl.P = M / g;
+    pl.dM = fold_div(M);
+    pl.dP = fold_div(pl.P);
+    pl.dg = fold_div(g);
+    pl.d1 = fold_div(1);
+    const std::vector<int> base = {2, 3, 4, 5, 6, 7, 8, 9, 10};
+    const std::vector<int> more[4] = {{}, {12, 15, 16}, {11, 13, 14}, {18, 20, 25}};
+    std::vector<int> f;
+    for (int c = 0; c < 4; ++c) {  // the class with the fewest stages, the smaller radices first
+        std::vector<int> set = base;
+        set.insert(set.end(), more[c].begin(), more[c].end());
+        const std::vector<int> t = fold_factors(pl.P, set, c == 2 ? 14 : 10);
+        if (t.empty() || (int)t.size() > kFoldStages) continue;
+        if (f.empty() || t.size() < f.size()) {
+            f = t;
+            pl.cls = c;
+        }
+    }
+    if (f.empty()) return false;
+    pl.n = (int)f.size();
+    // the largest factors in the plain stages, the smallest in the fused one, which holds two sets
+    // of values
+    std::reverse(f.begin(), f.end());
+    const int rl = f.back();
+    pl.dRl = fold_div(rl);
+    pl.pad = rl % 2 == 0 ? 1 : 0;
+    int m = pl.P;
+    for (int s = 0; s < pl.n; ++s) {
+        FoldStage& st = pl.st[s];
+        m /= f[s];
+        st.R = f[s];
+        st.nb = fold_div(pl.P / f[s]);
+        st.m = fold_div(m);
+        st.mp = s + 1 < pl.n ? m + pl.pad * (m / rl) : 1;
+        st.Lp = s + 1 < pl.n ? st.R * st.mp : rl + pl.pad;
+        st.tw = pl.ntw;
+        if (s + 1 < pl.n) pl.ntw += (f[s] - 1) * m;
+    }
+    return true;
+}
+
+size_t fold_lds_bytes(Kind kind, bool dbl, const FoldPlan& pl, const PassGeom& g) {
+    const size_t c = dbl ? 16 : 8, ts = (size_t)1 << g.flts, nrow = (size_t)g.fqr << g.flts;
+    size_t n = (size_t)pl.ntw + nrow * g.frs;
+    if (kind == Kind::EH) return (n + ts * g.fraw) * c;
+    if (!g.fdirect) n += ts * g.fraw;
+    if (kind == Kind::EA) n += ts * g.fraw + pl.g;
+    return n * c;
+}
+
+// Instructions of a step of `rows` rows, in wavefront instructions: every stage costs its butterflies
+// in full wavefronts, so few rows waste lanes in the stages with few butterflies. `stages`: barriers.
+static double fold_step_cost(Kind kind, const FoldPlan& pl, int rows, int gs, int& stages) {
+    auto waves = [&](int items) { return (double)((items + 63) / 64); };
+    const bool eh = kind == Kind::EH;
+    double c = 0;
+    stages = 0;
+    for (int s = 0; s < pl.n; ++s) {
+        const int R = pl.st[s].R, nb = pl.P / R;
+        if (s + 1 < pl.n) {
+            const double bf = 40.0 + 25.0 * R;
+            c += waves(rows * pl.g * nb) * bf + waves(rows * nb) * bf;
+            stages += 2;
+        } else {
+            const double grp = (double)((pl.g + gs - 1) / gs);
+            c += waves(rows * nb * gs) * (40.0 + (eh ? grp + 1 : grp) * 22.0 * R + 8.0 * R);
+            ++stages;
+            if (!eh && gs > 1) {
+                c += waves(rows * nb) * (40.0 + (12.0 + 4.0 * gs) * R);
+                ++stages;
+            }
+        }
+    }
+    return c;
+}
+
+// Tile and step sizes of a folded pass, into g; false (g is then as before) when one line and one term
+// do not fit the LDS. `cus`: compute units of the device.
+//
+// Every pair (lines per tile, terms per step) that fits the LDS is priced in cycles: a step takes its
+// instructions times the workgroups that share the CU, or, when too few do, its own instructions
+// plus a latency per barrier; the launch takes its rounds of resident workgroups times their steps.
+// The constants are instruction counts of the compiled kernels (FP64: 1.6 times, for its LDS traffic)
+// and a barrier-to-barrier latency (LDS exchange and table reads) of about 1200 cycles; measured times
+// are about 1.5 times the result.
+bool fold_geometry(Kind kind, bool dbl, const FoldPlan& pl, PassGeom& g, int cus) {
+    const int lim = lds_limit_bytes();
+    const PassGeom g0 = g;
+    g.fA = g.A;
+    if (g.S == 1) {  // contiguous lines of all slices in one row
+        g.A *= g.Qin;
+        g.Qin = 1;
+    }
+    const int rl = pl.st[pl.n - 1].R;
+    const int nb = pl.P / rl;
+    g.fps = nb * (rl + pl.pad);
+    g.fraw = pl.M | 1;
+    const int64_t lines = g.S == 1 ? g.A : g.S;
+    auto set = [&](int l, int qr, int gs, bool direct) {
+        g.flts = l;
+        g.fqr = qr;
+        g.fgs = gs;
+        g.dgs = fold_div(gs);
+        g.fdirect = direct;
+        // slots of a row: the subsequences (one factor: the groups' sums), EH with groups one more
+        int slots = pl.n == 1 ? (gs > 1 ? gs : 0) : pl.g;
+        if (kind == Kind::EH) slots = pl.g + (gs > 1 && pl.n > 1 ? 1 : 0);
+        g.frs = slots ? (slots * g.fps) | 1 : 0;
+        g.TS = 1 << l;
+        g.ntiles = g.S == 1 ? (g.A + g.TS - 1) / g.TS : g.A * ((g.S + g.TS - 1) / g.TS);
+        return (int64_t)fold_lds_bytes(kind, dbl, pl, g);
+    };
+    const int qmax = kind == Kind::EA ? std::min(g.qn, pl.g) : g.qn;
+    // strided lines: memory is read and written in pieces of 2^l elements; below 64 bytes it pays for
+    // the rest of them
+    const int cover = dbl ? 2 : 3;
+    const int regs = dbl ? (pl.cls < 2 ? 3 : 2) : 4;  // workgroups per CU by registers
+    double best = 0;
+    int bl = -1, bq = 1, bg = 1, bw = 1;
+    bool bd = false;
+    for (int l = 0; l < 8 && (l == 0 || (1 << (l - 1)) < lines); ++l) {
+        for (int qr = 1; qr <= qmax && (qr << l) <= 256; ++qr) {
+            const int rows = qr << l;
+            if ((int64_t)rows * pl.M * 2 >= (1 << 21)) break;
+            // groups of subsequences: as many as give every thread work in the last forward stage
+            const int gs = std::max(1, std::min(pl.g, (kThreads + rows * nb - 1) / (rows * nb)));
+            int stages = 0;
+            const double instr = fold_step_cost(kind, pl, rows, gs, stages) * (dbl ? 1.6 : 1.0);
+            for (int qpw = kind == Kind::E ? qr : g.qn;; qpw = std::min(g.qn, 2 * qpw)) {
+                bool direct = kind == Kind::E && qr == 1 && qpw == 1;
+                int64_t lds = set(l, qr, gs, direct);
+                if (lds > lim && kind != Kind::EH) lds = set(l, qr, gs, direct = true);
+                if (lds > lim) break;
+                const double wgs = (double)(g.Qin * g.ntiles) * ((g.qn + qpw - 1) / qpw);
+                const int steps = (qpw + qr - 1) / qr;
+                const double resident = std::min(std::min((double)(lim / std::max<int64_t>(lds, 1)), (double)regs),
+                                                 std::ceil(wgs / cus));
+                const double rounds = std::ceil(wgs / (cus * resident));
+                // the tile in (and for EA and EH out) once
+                const double io = pl.M * (double)(1 << l) / 64.0 * (kind == Kind::E ? (direct ? 6.0 : 12.0) : 24.0);
+                auto span = [&](double in, double lat) { return std::max(resident * in, in + lat); };
+                double cost = rounds * (steps * span(instr, 1200.0 * stages) + span(io, 3000.0));
+                if (g.S != 1 && l < cover) cost *= 1.0 + 0.25 * ((1 << (cover - l)) - 1);
+                if (bl < 0 || cost < best) {
+                    best = cost;
+                    bl = l;
+                    bq = qr;
+                    bg = gs;
+                    bw = qpw;
+                    bd = direct;
+                }
+                if (qpw >= g.qn) break;
+            }
+        }
+    }
+    if (bl < 0) {
+        g = g0;
+        return false;
+    }
+    g.fqpw = bw;
+    g.fcycles = best;
+    set(bl, bq, bg, bd);
+    return true;
+}
+
+hipError_t launch_pass_fold(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
+                            int accumulate, void* rho, hipStream_t st) {
+    if (!ax.fold || !ax.foldd || !ax.FT || !g.fold || g.TS != (1 << g.flts)) return hipErrorInvalidValue;
+    if ((int64_t)fold_lds_bytes(kind, dbl, *ax.fold, g) > lds_limit_bytes()) return hipErrorInvalidValue;
+    switch (ax.fold->cls) {
+        case 0:
+            return dbl ? launch_fold_T<double, 0>(kind, in, out, ax, g, accumulate, rho, st)
+                       : launch_fold_T<float, 0>(kind, in, out, ax, g, accumulate, rho, st);
+        case 1:
+            return dbl ? launch_fold_T<double, 1>(kind, in, out, ax, g, accumulate, rho, st)
+                       : launch_fold_T<float, 1>(kind, in, out, ax, g, accumulate, rho, st);
+        case 3:
+            return dbl ? launch_fold_T<double, 3>(kind, in, out, ax, g, accumulate, rho, st)
+                       : launch_fold_T<float, 3>(kind, in, out, ax, g, accumulate, rho, st);
+        default:
+            return dbl ? launch_fold_T<double, 2>(kind, in, out, ax, g, accumulate, rho, st)
+                       : launch_fold_T<float, 2>(kind, in, out, ax, g, accumulate, rho, st);
+    }
+}
+
+}  // namespace fx

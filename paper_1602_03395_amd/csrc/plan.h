@@ -1,6 +1,7 @@
 // Plan object and schedule helpers shared by the host runtime files (not public ABI).
 #pragma once
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -39,6 +40,7 @@ struct fx_plan {
     int64_t len[3] = {1, 1, 1};   // padded shape
     fx::AxisParams par[3];
     fx::AxisDev ax[3];
+    fx::FoldPlan foldp[3];         // plans of the folded line kernels (ax[i].fold points here)
     int act[3] = {0, 0, 0};
     int nact = 0;
     int64_t M = 1;                 // total points
@@ -63,6 +65,17 @@ struct fx_plan {
     void* bf_state = nullptr;      // brute-force comparator: tables and buffers (built on first use)
     bool use_cfp = true;           // register E kernel where the pruned length allows it
     bool use_asr = true;           // register structured accumulate (k_ASR) for g <= asr_max_g
+    struct FoldMemo {              // tile of a folded pass (see fold_geometry_of)
+        fx::Kind kind;
+        int axis;
+        int64_t Qin, A, S;
+        int qn;
+        bool ok;
+        fx::PassGeom g;
+    };
+    mutable std::mutex fold_mu;
+    mutable std::vector<FoldMemo> fold_memo;
+    bool use_fold = true;          // folded line kernels where no register kernel applies (FX_FOLD=0 disables)
     bool use_eh2 = true;           // compile-time power-of-two EH kernel (FX_NO_EH2 disables)
     int use_aa = 1;                // fuse the last two accumulate passes: 0 never (FX_AA=0), 1 in
                                    // registers where g_u = g_v is 16 or 32 and they are the last two

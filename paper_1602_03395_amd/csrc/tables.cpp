@@ -58,6 +58,11 @@ inline void put(std::vector<double>& v, size_t i, double cycles, double amp) {
     v[2 * i + 1] = amp * std::sin(ang);
 }
 
+int64_t gcd_of(int64_t g, int64_t b) {
+    while (b) { const int64_t r = g % b; g = b; b = r; }
+    return g;
+}
+
 // Chirp-folded table of the register E kernel. With g = gcd(lam, M), P = M / g, input index
 // n = g n1 + n2 and spectral index m = r + P c (n1, r < P; n2, c < g), the forward DFT factors as
 //   Y[r + P c] = sum_n2 w_g^(n2 c) w_M^(n2 r) V[n2][r],  V[n2][r] = sum_n1 w_P^(n1 r) y[g n1 + n2],
@@ -68,8 +73,7 @@ inline void put(std::vector<double>& v, size_t i, double cycles, double amp) {
 // are folded in as well. Layout [q][r][n2] (the g lanes of a line read consecutive values, and the
 // P g = M values of one q are contiguous), FP64 complex.
 void build_ht(AxisTables& t, int64_t M, int64_t lam) {
-    int64_t g = lam, b = M;
-    while (b) { const int64_t r = g % b; g = b; b = r; }
+    const int64_t g = gcd_of(lam, M);
     const int64_t P = M / g;
     const int64_t N = lam * M;
     t.HT.assign(2 * (size_t)(lam * M), 0.0);
@@ -87,15 +91,27 @@ void build_ht(AxisTables& t, int64_t M, int64_t lam) {
                     sr += z[0] * w[0] - z[1] * w[1];
                     si += z[0] * w[1] + z[1] * w[0];
                 }
+                const size_t i = at(q, r, n2);
+                if (n2 == 0) {
+                    t.HT[i] = sr * (1.0 / (double)M);
+                    t.HT[i + 1] = si * (1.0 / (double)M);
+                    continue;
+                }
                 // exp(-2 pi i (n2 r lam + q n2) / (lam M)) / M
                 const double ang = -kTwoPi * rational_cycles(n2 * r * lam + q * n2, N);
                 const double er = std::cos(ang) / (double)M, ei = std::sin(ang) / (double)M;
-                const size_t i = at(q, r, n2);
                 t.HT[i] = sr * er - si * ei;
                 t.HT[i + 1] = sr * ei + si * er;
             }
         }
     }
+}
+
+// The copies of HT that the register kernels read.
+void arrange_ht(AxisTables& t, int64_t M, int64_t lam) {
+    const int64_t g = gcd_of(lam, M);
+    const int64_t P = M / g;
+    auto at = [&](int64_t q, int64_t r, int64_t n2) { return 2 * (size_t)((q * P + r) * g + n2); };
     // Second copy for the forward register kernels. Their first cross-lane reduction step pairs
     // lanes n2 and n2 ^ 1; the odd lane keeps the upper half of the P sums. When the odd lane's
     // P values come with their halves exchanged, both lanes keep the lower half and send the upper
@@ -144,6 +160,48 @@ void build_ht(AxisTables& t, int64_t M, int64_t lam) {
                 t.HTl[d + 1] = from[src + 1];
             }
         }
+}
+
+// Table of the folded line kernels: per term the g rows HT_q[n2] with the spectrum in the digit-reversed
+// order in which the plan's forward stages leave it, the premultiplying phases of the subsequences
+// TA_q[g n1], and Tf_q[n0(u)] at the output n0(u) < P that reads sample u; then the twiddles
+// exp(-2 pi i k u / L) of every stage but the last, [u - 1][k] with u < R, k < m, L = R m.
+void build_ft(AxisTables& t, int64_t lam, const FoldPlan& pl) {
+    const int64_t M = pl.M, g = pl.g, P = pl.P;
+    const int64_t lg = (lam / g) % P;
+    t.FT.assign(2 * (size_t)(lam * (g + 2) * P + pl.ntw), 0.0);
+    std::vector<int64_t> n0((size_t)P, 0), rev((size_t)P, 0);
+    for (int64_t n = 0; n < P; ++n) n0[(size_t)((n * lg) % P)] = n;
+    for (int64_t p = 0; p < P; ++p) {
+        // position p = sum_s u_s m_s holds frequency r = u_0 + R_0 (u_1 + R_1 (...))
+        int64_t rest = p, r = 0, w = 1;
+        for (int s = 0; s < pl.n; ++s) {
+            r += (rest / pl.st[s].m.d) * w;
+            rest %= pl.st[s].m.d;
+            w *= pl.st[s].R;
+        }
+        rev[(size_t)p] = r;
+    }
+    for (int64_t q = 0; q < lam; ++q) {
+        double* row = &t.FT[2 * (size_t)(q * (g + 2) * P)];
+        auto set = [&](int64_t at, const std::vector<double>& v, int64_t i) {
+            row[2 * at] = v[2 * (size_t)i];
+            row[2 * at + 1] = v[2 * (size_t)i + 1];
+        };
+        for (int64_t n2 = 0; n2 < g; ++n2)
+            for (int64_t p = 0; p < P; ++p) set(n2 * P + p, t.HT, (q * P + rev[(size_t)p]) * g + n2);
+        for (int64_t n1 = 0; n1 < P; ++n1) {
+            set(M + n1, t.TA, q * M + g * n1);
+            set(M + P + n1, t.Tf, q * M + n0[(size_t)n1]);
+        }
+    }
+    const size_t tw0 = (size_t)(lam * (g + 2) * P);
+    for (int s = 0; s + 1 < pl.n; ++s) {
+        const int64_t m = pl.st[s].m.d, R = pl.st[s].R;
+        for (int64_t u = 1; u < R; ++u)
+            for (int64_t k = 0; k < m; ++k)
+                put(t.FT, tw0 + (size_t)(pl.st[s].tw + (u - 1) * m + k), -rational_cycles(k * u, R * m), 1.0);
+    }
 }
 
 }  // namespace
@@ -195,7 +253,10 @@ AxisTables build_axis_tables(const AxisParams& p) {
         }
     }
     for (int64_t k = 0; k < M; ++k) put(t.tw, (size_t)k, -rational_cycles(k, M), 1.0);
-    if (p.want_ht) build_ht(t, M, lam);
+    if (p.want_ht || p.fold) build_ht(t, M, lam);
+    if (p.fold) build_ft(t, lam, *p.fold);
+    if (p.want_ht) arrange_ht(t, M, lam);
+    else t.HT.clear();
     return t;
 }
 
