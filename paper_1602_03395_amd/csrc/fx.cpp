@@ -182,6 +182,13 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
         g.qn = qn[ax];
         const bool reg_eh = kind == Kind::EH && p->use_cfp && p->ax[ax].HT != nullptr && qn[ax] <= 64 &&
                             ehr_applicable(p->ax[ax].M, p->ax[ax].g);
+        g.eal = kind == Kind::EA && p->use_cfp && p->use_eal && p->ax[ax].LT != nullptr && g.S > 1 &&
+                (g.Qin * g.A * g.S + eal_tile_lines() - 1) / eal_tile_lines() >= num_cus() / 2;
+        if (g.eal) {
+            g.TS = eal_tile_lines();
+            g.ntiles = (g.Qin * g.A * g.S + g.TS - 1) / g.TS;
+            return g;
+        }
         g.eaw = kind == Kind::EA && p->use_cfp && p->use_eaw && p->ax[ax].HTx != nullptr &&
                 eaw_applicable(p->dbl, p->ax[ax].M, p->ax[ax].g, qn[ax]);
         g.erw = kind == Kind::E && p->use_cfp && p->use_erw > 0 && p->ax[ax].HT != nullptr && g.S == 1 &&
@@ -304,7 +311,7 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
     auto do_EA = [&](int ax) {
         // the structured EA kernel spreads the terms over the waves of a workgroup: never split
         const PassGeom ge = geom(Kind::EA, ax, slices);
-        if (!ge.eas && (split(Kind::EA, ax) || fold_split(ge, ax))) { do_E(ax); do_A(ax); return; }
+        if (!ge.eas && !ge.eal && (split(Kind::EA, ax) || fold_split(ge, ax))) { do_E(ax); do_A(ax); return; }
         emit(Kind::EA, ax, ge, vol());
     };
     // the adjoint of EA runs as AH + EH when both have register forms (each is cheaper than the
@@ -701,6 +708,7 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
         // all have register forms, nor for one whose rows would take more than 400 MB.
         const bool reg = (cfp_applicable(Kind::E, p->dbl, ad.M, ad.g) || erg_applicable(p->dbl, ad.M, ad.g)) &&
                          ((ehr_applicable(ad.M, ad.g) && ad.lam <= 64) || erg_applicable(p->dbl, ad.M, ad.g));
+        ap.want_lt = eal_applicable(p->dbl, ad.M, ad.g) && ap.lam * ap.M <= (int64_t(1) << 22);
         if (!reg && !(ad.M == 1 && ad.lam == 1) && ap.lam * ap.M <= (int64_t(1) << 23) &&
             ap.lam * ap.M * (int64_t)ad.g <= (int64_t(1) << 26) && make_fold_plan(p->foldp[pa], ad.M, ad.g)) {
             ad.fold = &p->foldp[pa];
@@ -721,30 +729,36 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
             return FX_EUNSUPPORTED;
         }
     }
-    // Upload all tables in one allocation: per axis TA | TB | Tf | tw | HT | HTx | HTl | FT.
+    // Upload all tables in one allocation: per axis TA | TB | Tf | tw | HT | HTx | HTl | FT | LT | LR.
     const size_t cs = csize(p);
     size_t total = 0;
-    constexpr int kTabs = 8;
+    constexpr int kTabs = 9;
     size_t offs[3][kTabs];
     for (int pa = 0; pa < 3; ++pa) {
         const size_t lm = (size_t)p->ax[pa].lam * p->ax[pa].M;
         const size_t sz[kTabs] = {lm, lm, lm, (size_t)p->ax[pa].M, tabs[pa].HT.size() / 2, tabs[pa].HTx.size() / 2,
-                                  tabs[pa].HTl.size() / 2, tabs[pa].FT.size() / 2};
+                                  tabs[pa].HTl.size() / 2, tabs[pa].FT.size() / 2, tabs[pa].LT.size() / 2};
         for (int t = 0; t < kTabs; ++t) {
             offs[pa][t] = total;
             total += ((sz[t] * cs + 255) / 256) * 256;
         }
     }
-    size_t poff[3];  // plans of the folded line kernels
+    size_t poff[3], roff[3];  // plans of the folded line kernels, output rows of the lane-per-line EA
     for (int pa = 0; pa < 3; ++pa) {
         poff[pa] = total;
         total += ((sizeof(FoldPlan) + 255) / 256) * 256;
+        roff[pa] = total;
+        total += ((tabs[pa].LR.size() * sizeof(int) + 255) / 256) * 256;
     }
     std::vector<unsigned char> host(total, 0);
-    for (int pa = 0; pa < 3; ++pa) std::memcpy(host.data() + poff[pa], &p->foldp[pa], sizeof(FoldPlan));
+    for (int pa = 0; pa < 3; ++pa) {
+        std::memcpy(host.data() + poff[pa], &p->foldp[pa], sizeof(FoldPlan));
+        if (!tabs[pa].LR.empty()) std::memcpy(host.data() + roff[pa], tabs[pa].LR.data(), tabs[pa].LR.size() * sizeof(int));
+    }
     for (int pa = 0; pa < 3; ++pa) {
         const std::vector<double>* src[kTabs] = {&tabs[pa].TA, &tabs[pa].TB,  &tabs[pa].Tf,  &tabs[pa].tw,
-                                                 &tabs[pa].HT, &tabs[pa].HTx, &tabs[pa].HTl, &tabs[pa].FT};
+                                                 &tabs[pa].HT, &tabs[pa].HTx, &tabs[pa].HTl, &tabs[pa].FT,
+                                                 &tabs[pa].LT};
         for (int t = 0; t < kTabs; ++t) {
             if (p->dbl) to_prec<double>(*src[t], host, offs[pa][t]);
             else to_prec<float>(*src[t], host, offs[pa][t]);
@@ -774,6 +788,8 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
         p->ax[pa].HTl = tabs[pa].HTl.empty() ? nullptr : b + offs[pa][6];
         p->ax[pa].FT = tabs[pa].FT.empty() ? nullptr : b + offs[pa][7];
         p->ax[pa].foldd = (const FoldPlan*)(b + poff[pa]);
+        p->ax[pa].LT = tabs[pa].LT.empty() ? nullptr : b + offs[pa][8];
+        p->ax[pa].LR = tabs[pa].LR.empty() ? nullptr : (const int*)(b + roff[pa]);
     }
     size_t budget = (size_t)8 << 30;
     if (const char* e = std::getenv("FX_WORKSPACE_MB")) budget = (size_t)std::max(1L, std::atol(e)) << 20;
@@ -791,6 +807,7 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
     if (std::getenv("FX_NO_EAW")) p->use_eaw = false;
     if (const char* e = std::getenv("FX_ERW")) p->use_erw = std::atoi(e);
     if (std::getenv("FX_NO_EH2")) p->use_eh2 = false;
+    if (const char* e = std::getenv("FX_EAL")) p->use_eal = (e[0] != '0');
     if (const char* e = std::getenv("FX_FOLD")) p->use_fold = (e[0] != '0');
     if (const char* e = std::getenv("FX_ASR_MAXG")) p->asr_max_g = std::max(1, std::atoi(e));
     p->cfp_blocks = 2 * num_cus();
@@ -1091,6 +1108,7 @@ const char* kernel_of(const fx_plan* p, const Op& o) {
     if (o.kind == Kind::E && g.erw) return "k_ERW";
     if ((o.kind == Kind::E || o.kind == Kind::EA) && g.erg) return "k_ERG";
     if (o.kind == Kind::EH && g.erg) return "k_EHG";
+    if (o.kind == Kind::EA && g.eal) return "k_EAL";
     if (o.kind == Kind::EA && g.eaw) return "k_EAW";
     if (o.kind == Kind::EA && g.eas) return "k_EAS";
     if (g.qc > 0 && o.kind == Kind::EH) return "k_EHR";
@@ -1144,10 +1162,10 @@ fx_status fx_plan_describe(const fx_plan* p, char* buf, size_t len) {
                       "\"A\":%lld,\"S\":%lld,\"TS\":%d,\"reg\":%d",
                       i ? "," : "", names[(int)o.kind], o.axis - (3 - p->ndim), a.M, a.P, a.lam, o.g.qn,
                       (long long)o.g.Qin, (long long)o.g.A, (long long)o.g.S, o.g.TS,
-                      (o.g.qc > 0 || o.g.reg_a || o.g.eas || o.g.eaw) ? 1 : 0);
+                      (o.g.qc > 0 || o.g.reg_a || o.g.eas || o.g.eaw || o.g.eal) ? 1 : 0);
         s += tmp;
         s += std::string(",\"kernel\":\"") + kernel_of(p, o) + "\"";
-        if (o.g.eas || o.g.eaw || (o.g.erg && o.kind == Kind::EA)) s += ",\"eas\":1";
+        if (o.g.eas || o.g.eaw || o.g.eal || (o.g.erg && o.kind == Kind::EA)) s += ",\"eas\":1";
         if (o.g.eh2) s += ",\"eh2\":1";
         if (o.g.fold) {  // lines and terms per step, groups of subsequences, terms per workgroup
             std::snprintf(tmp, sizeof(tmp), ",\"step\":[%d,%d,%d,%d]", 1 << o.g.flts, o.g.fqr, o.g.fgs, o.g.fqpw);

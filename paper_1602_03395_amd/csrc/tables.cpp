@@ -204,6 +204,43 @@ void build_ft(AxisTables& t, int64_t lam, const FoldPlan& pl) {
     }
 }
 
+// Table of the lane-per-line EA kernel. With k = (q - q mod g) / g and rho0 = -k (lam / g)^-1 mod P, per
+// term q the phases exp(-2 pi i b (q + lam rho0) / (lam P)), b = 1..P-1 (the premultiplying phase of
+// (presA) on the subsequences and the modulation that moves spectral index rho0 + r' to slot r'), then
+// D[n2][r'] = Tf_q[0] HT_q[n2][(r' + rho0) mod P]. Behind the terms TW[f][j] = exp(2 pi i j c1(f) / M):
+// the P-point inverse transform over the slots leaves at f the output c1(f) = f (lam / g)^-1 mod P (and
+// those P apart). LR[f][c2] = c1(f) + P c2, the output row of the final g-point transform.
+void build_lt(AxisTables& t, int64_t M, int64_t lam) {
+    const int64_t g = gcd_of(lam, M), P = M / g, lg = (lam / g) % P;
+    int64_t inv = 0;
+    for (int64_t x = 0; x < P; ++x)
+        if ((x * lg) % P == 1 % P) { inv = x; break; }
+    const int64_t row = M + P - 1;
+    t.LT.assign(2 * (size_t)(lam * row + M), 0.0);
+    t.LR.assign((size_t)M, 0);
+    for (int64_t q = 0; q < lam; ++q) {
+        const int64_t k = q / g;
+        const int64_t rho0 = (P - (k % P) * inv % P) % P;
+        for (int64_t b = 1; b < P; ++b)
+            put(t.LT, (size_t)(q * row + b - 1), -rational_cycles(b * (q + lam * rho0), lam * P), 1.0);
+        const double fr = t.Tf[2 * (size_t)(q * M)], fi = t.Tf[2 * (size_t)(q * M) + 1];
+        for (int64_t n2 = 0; n2 < g; ++n2)
+            for (int64_t r = 0; r < P; ++r) {
+                const double* h = &t.HT[2 * (size_t)((q * P + (r + rho0) % P) * g + n2)];
+                double* d = &t.LT[2 * (size_t)(q * row + P - 1 + n2 * P + r)];
+                d[0] = fr * h[0] - fi * h[1];
+                d[1] = fr * h[1] + fi * h[0];
+            }
+    }
+    for (int64_t f = 0; f < P; ++f) {
+        const int64_t c1 = (f * inv) % P;
+        for (int64_t j = 0; j < g; ++j) {
+            put(t.LT, (size_t)(lam * row + f * g + j), rational_cycles(j * c1, M), 1.0);
+            t.LR[(size_t)(f * g + j)] = (int)(c1 + P * j);
+        }
+    }
+}
+
 }  // namespace
 
 AxisTables build_axis_tables(const AxisParams& p) {
@@ -253,7 +290,8 @@ AxisTables build_axis_tables(const AxisParams& p) {
         }
     }
     for (int64_t k = 0; k < M; ++k) put(t.tw, (size_t)k, -rational_cycles(k, M), 1.0);
-    if (p.want_ht || p.fold) build_ht(t, M, lam);
+    if (p.want_ht || p.want_lt || p.fold) build_ht(t, M, lam);
+    if (p.want_lt) build_lt(t, M, lam);
     if (p.fold) build_ft(t, lam, *p.fold);
     if (p.want_ht) arrange_ht(t, M, lam);
     else t.HT.clear();
