@@ -182,11 +182,23 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
         g.qn = qn[ax];
         const bool reg_eh = kind == Kind::EH && p->use_cfp && p->ax[ax].HT != nullptr && qn[ax] <= 64 &&
                             ehr_applicable(p->ax[ax].M, p->ax[ax].g);
-        g.eal = kind == Kind::EA && p->use_cfp && p->use_eal && p->ax[ax].LT != nullptr && g.S > 1 &&
-                (g.Qin * g.A * g.S + eal_tile_lines() - 1) / eal_tile_lines() >= num_cus() / 2;
-        if (g.eal) {
-            g.TS = eal_tile_lines();
-            g.ntiles = (g.Qin * g.A * g.S + g.TS - 1) / g.TS;
+        const int64_t ltiles = (g.Qin * g.A * g.S + lane_tile_lines() - 1) / lane_tile_lines();
+        // One line per lane: strided lines (a wave reads 64 neighbours), and enough of them for about two waves
+        // per CU, since a wave runs its share of the terms one after the other. Measured with 16 to 512
+        // tiles (EA of 64 points, 40 terms, FP32): 16 tiles of 8 waves 17.7 us as E + A against 19.0, 32 tiles 21.7
+        // against 19.9, 64 tiles 30.7 (k_EAW) against 19.5, 512 tiles 52.8 against 38.8; the adjoint crosses
+        // between 32 and 64 tiles, E between 16 and 64.
+        const int64_t lwaves = ltiles * (kind == Kind::EA ? (int64_t)p->ax[ax].g * eal_halves(p->dbl, p->ax[ax].M, p->ax[ax].g)
+                                                          : 8);
+        const bool lanes = p->use_cfp && p->use_eal && g.S > 1 && lwaves >= 2 * num_cus();
+        g.eal = lanes && (kind == Kind::EA || kind == Kind::EAH) && p->ax[ax].LT != nullptr;
+        g.el = lanes && kind == Kind::E && p->ax[ax].ET != nullptr;
+        if (g.eal || g.el) {
+            g.TS = lane_tile_lines();
+            g.ntiles = ltiles;
+            // E: terms per workgroup, in whole rounds of its eight waves, for about four workgroups per CU
+            const int64_t w = ltiles * g.qn / (4 * (int64_t)num_cus());
+            g.fqpw = (int)std::min<int64_t>(g.qn, std::max<int64_t>(8, (w + 7) / 8 * 8));
             return g;
         }
         g.eaw = kind == Kind::EA && p->use_cfp && p->use_eaw && p->ax[ax].HTx != nullptr &&
@@ -322,6 +334,10 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
                qn[ax] <= 64 && ehr_applicable(a.M, a.g);
     };
     auto do_EAH = [&](int ax) {
+        if (geom(Kind::EAH, ax, slices).eal) {
+            emit(Kind::EAH, ax, geom(Kind::EAH, ax, slices), vol());
+            return;
+        }
         // also split where EH has its compile-time power-of-two kernel (the fused generic pass
         // runs one transform chain per term and workgroup)
         const bool eh2 = p->use_eh2 && eh2_applicable(p->ax[ax].M, p->ax[ax].P);
@@ -708,7 +724,11 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
         // all have register forms, nor for one whose rows would take more than 400 MB.
         const bool reg = (cfp_applicable(Kind::E, p->dbl, ad.M, ad.g) || erg_applicable(p->dbl, ad.M, ad.g)) &&
                          ((ehr_applicable(ad.M, ad.g) && ad.lam <= 64) || erg_applicable(p->dbl, ad.M, ad.g));
-        ap.want_lt = eal_applicable(p->dbl, ad.M, ad.g) && ap.lam * ap.M <= (int64_t(1) << 22);
+        // lane-per-line kernels: for axes whose lines can be strided
+        if (pa < 2 && ap.lam * ap.M <= (int64_t(1) << 22)) {
+            if (eal_applicable(p->dbl, ad.M, ad.g)) ap.lt_halves = eal_halves(p->dbl, ad.M, ad.g);
+            ap.want_et = el_applicable(p->dbl, ad.M, ad.g);
+        }
         if (!reg && !(ad.M == 1 && ad.lam == 1) && ap.lam * ap.M <= (int64_t(1) << 23) &&
             ap.lam * ap.M * (int64_t)ad.g <= (int64_t(1) << 26) && make_fold_plan(p->foldp[pa], ad.M, ad.g)) {
             ad.fold = &p->foldp[pa];
@@ -729,15 +749,16 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
             return FX_EUNSUPPORTED;
         }
     }
-    // Upload all tables in one allocation: per axis TA | TB | Tf | tw | HT | HTx | HTl | FT | LT | LR.
+    // Upload all tables in one allocation: per axis TA | TB | Tf | tw | HT | HTx | HTl | FT | LT | ET, then plans and rows.
     const size_t cs = csize(p);
     size_t total = 0;
-    constexpr int kTabs = 9;
+    constexpr int kTabs = 10;
     size_t offs[3][kTabs];
     for (int pa = 0; pa < 3; ++pa) {
         const size_t lm = (size_t)p->ax[pa].lam * p->ax[pa].M;
         const size_t sz[kTabs] = {lm, lm, lm, (size_t)p->ax[pa].M, tabs[pa].HT.size() / 2, tabs[pa].HTx.size() / 2,
-                                  tabs[pa].HTl.size() / 2, tabs[pa].FT.size() / 2, tabs[pa].LT.size() / 2};
+                                  tabs[pa].HTl.size() / 2, tabs[pa].FT.size() / 2, tabs[pa].LT.size() / 2,
+                                  tabs[pa].ET.size() / 2};
         for (int t = 0; t < kTabs; ++t) {
             offs[pa][t] = total;
             total += ((sz[t] * cs + 255) / 256) * 256;
@@ -758,7 +779,7 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
     for (int pa = 0; pa < 3; ++pa) {
         const std::vector<double>* src[kTabs] = {&tabs[pa].TA, &tabs[pa].TB,  &tabs[pa].Tf,  &tabs[pa].tw,
                                                  &tabs[pa].HT, &tabs[pa].HTx, &tabs[pa].HTl, &tabs[pa].FT,
-                                                 &tabs[pa].LT};
+                                                 &tabs[pa].LT, &tabs[pa].ET};
         for (int t = 0; t < kTabs; ++t) {
             if (p->dbl) to_prec<double>(*src[t], host, offs[pa][t]);
             else to_prec<float>(*src[t], host, offs[pa][t]);
@@ -789,6 +810,7 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
         p->ax[pa].FT = tabs[pa].FT.empty() ? nullptr : b + offs[pa][7];
         p->ax[pa].foldd = (const FoldPlan*)(b + poff[pa]);
         p->ax[pa].LT = tabs[pa].LT.empty() ? nullptr : b + offs[pa][8];
+        p->ax[pa].ET = tabs[pa].ET.empty() ? nullptr : b + offs[pa][9];
         p->ax[pa].LR = tabs[pa].LR.empty() ? nullptr : (const int*)(b + roff[pa]);
     }
     size_t budget = (size_t)8 << 30;
@@ -1108,7 +1130,8 @@ const char* kernel_of(const fx_plan* p, const Op& o) {
     if (o.kind == Kind::E && g.erw) return "k_ERW";
     if ((o.kind == Kind::E || o.kind == Kind::EA) && g.erg) return "k_ERG";
     if (o.kind == Kind::EH && g.erg) return "k_EHG";
-    if (o.kind == Kind::EA && g.eal) return "k_EAL";
+    if (g.eal) return o.kind == Kind::EA ? "k_EAL" : "k_EAHL";
+    if (g.el) return "k_EL";
     if (o.kind == Kind::EA && g.eaw) return "k_EAW";
     if (o.kind == Kind::EA && g.eas) return "k_EAS";
     if (g.qc > 0 && o.kind == Kind::EH) return "k_EHR";
@@ -1162,7 +1185,7 @@ fx_status fx_plan_describe(const fx_plan* p, char* buf, size_t len) {
                       "\"A\":%lld,\"S\":%lld,\"TS\":%d,\"reg\":%d",
                       i ? "," : "", names[(int)o.kind], o.axis - (3 - p->ndim), a.M, a.P, a.lam, o.g.qn,
                       (long long)o.g.Qin, (long long)o.g.A, (long long)o.g.S, o.g.TS,
-                      (o.g.qc > 0 || o.g.reg_a || o.g.eas || o.g.eaw || o.g.eal) ? 1 : 0);
+                      (o.g.qc > 0 || o.g.reg_a || o.g.eas || o.g.eaw || o.g.eal || o.g.el) ? 1 : 0);
         s += tmp;
         s += std::string(",\"kernel\":\"") + kernel_of(p, o) + "\"";
         if (o.g.eas || o.g.eaw || o.g.eal || (o.g.erg && o.kind == Kind::EA)) s += ",\"eas\":1";

@@ -65,6 +65,7 @@ struct AxisDev {
                                // P <= min(g, 8) row n2 turned by bitrev(n2 mod P), else HTx reordered
     const void* LT = nullptr;  // table of the lane-per-line EA (or null)
     const int* LR = nullptr;   // its output rows
+    const void* ET = nullptr;  // table of the lane-per-line E (or null)
     const void* FT = nullptr;  // table of the folded line kernels (or null)
     const FoldPlan* fold = nullptr;   // plan of those kernels (or null): host copy
     const FoldPlan* foldd = nullptr;  // and device copy
@@ -97,7 +98,8 @@ struct PassGeom {
     bool erw = false;    // E pass (g = 8, P = 16..64, contiguous lines): register form, a line per 8 P / V lanes
     bool erg = false;    // E, EA or EH pass (g = 2, 4, 8; P = 16..64): register form, a line per g P / 8 lanes
     bool eh2 = false;    // EH pass: compile-time power-of-two kernel, one output line per workgroup
-    bool eal = false;    // EA pass: one line per lane, 64 lines and a wave per residue of the terms per workgroup
+    bool eal = false;    // EA or EAH pass: one line per lane, tiles of 64 lines over all slices
+    bool el = false;     // E pass: one line per lane, fqpw terms per workgroup
     // E, EA or EH pass by the folded line kernels: 2^flts lines and fqr terms per step, fqpw terms per
     // workgroup (E), fgs groups of subsequences summed side by side, input read from global memory
     // instead of an LDS copy (fdirect); LDS strides of a slot, a row and a raw line. For contiguous
@@ -161,6 +163,7 @@ struct AxisTables {
     std::vector<double> HTl;             // [lam][g][P], rows turned for the rotated reduction (see build_ht)
     std::vector<double> LT;              // terms and twiddles of the lane-per-line EA (see build_lt)
     std::vector<int> LR;                 // its output rows
+    std::vector<double> ET;              // terms of the lane-per-line E (see build_et)
     std::vector<double> FT;              // rows and stage twiddles of the folded line kernels (see build_ft)
 };
 struct AxisParams {
@@ -172,7 +175,8 @@ struct AxisParams {
     // number l = i - floor(lam M / 2); NULL keeps hbar t kappa^2 / 2m.
     const double* phase = nullptr;
     bool want_ht = false;  // also build the chirp-folded table HT in its register-kernel layouts
-    bool want_lt = false;  // also build the table of the lane-per-line EA
+    int lt_halves = 0;     // > 0: also build the table of the lane-per-line EA, this many classes of slots
+    bool want_et = false;  // also build the table of the lane-per-line E
     const FoldPlan* fold = nullptr;  // also build the rows of the folded line kernels for this plan
 };
 AxisTables build_axis_tables(const AxisParams& p);
@@ -247,11 +251,15 @@ size_t fold_lds_bytes(Kind kind, bool dbl, const FoldPlan& pl, const PassGeom& g
 hipError_t launch_pass_fold(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
                             int accumulate, void* rho, hipStream_t st);
 
-// EA with one line per lane (kernels_lane.hip): P and g compiled in, tiles of 64 lines over all slices.
+// One line per lane (kernels_lane.hip), tiles of 64 lines over all slices: EA and its adjoint EAH with P and
+// g compiled in, E with P compiled in.
 bool eal_applicable(bool dbl, int M, int g);
-int eal_tile_lines();
-hipError_t launch_pass_eal(bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g, int accumulate,
-                           void* rho, hipStream_t st);
+int eal_halves(bool dbl, int M, int g);
+bool el_applicable(bool dbl, int M, int g);
+int lane_tile_lines();
+hipError_t launch_pass_eal(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
+                           int accumulate, void* rho, hipStream_t st);
+hipError_t launch_pass_el(bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g, hipStream_t st);
 
 void set_error(const std::string& msg);
 

@@ -735,7 +735,8 @@ size_t pass_lds_bytes(Kind kind, bool dbl, int TS, int M) {
 
 hipError_t launch_pass(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
                        int accumulate, void* rho, hipStream_t st) {
-    if (kind == Kind::EA && g.eal) return launch_pass_eal(dbl, in, out, ax, g, accumulate, rho, st);
+    if (g.eal) return launch_pass_eal(kind, dbl, in, out, ax, g, accumulate, rho, st);
+    if (g.el) return launch_pass_el(dbl, in, out, ax, g, st);
     // tile kernels index their tiles with 32-bit integers (the count includes the padding of the
     // XCD-aware order of the register E kernel)
     if (((g.Qin * g.ntiles + 7) / 8) * 8 * g.qn >= (int64_t(1) << 31)) return hipErrorInvalidValue;

@@ -204,40 +204,66 @@ void build_ft(AxisTables& t, int64_t lam, const FoldPlan& pl) {
     }
 }
 
-// Table of the lane-per-line EA kernel. With k = (q - q mod g) / g and rho0 = -k (lam / g)^-1 mod P, per
-// term q the phases exp(-2 pi i b (q + lam rho0) / (lam P)), b = 1..P-1 (the premultiplying phase of
-// (presA) on the subsequences and the modulation that moves spectral index rho0 + r' to slot r'), then
-// D[n2][r'] = Tf_q[0] HT_q[n2][(r' + rho0) mod P]. Behind the terms TW[f][j] = exp(2 pi i j c1(f) / M):
-// the P-point inverse transform over the slots leaves at f the output c1(f) = f (lam / g)^-1 mod P (and
-// those P apart). LR[f][c2] = c1(f) + P c2, the output row of the final g-point transform.
-void build_lt(AxisTables& t, int64_t M, int64_t lam) {
-    const int64_t g = gcd_of(lam, M), P = M / g, lg = (lam / g) % P;
+// Table of the lane-per-line EA kernel. With k = (q - q mod g) / g and rho0 = -k (lam / g)^-1 mod P, the
+// spectral index in slot r' of term q is r' + rho0 mod P. The slots are taken in `halves` interleaved
+// classes h (r' = h + halves r''), P1 = P / halves each. Per term and class: with two classes the factor
+// exp(-i pi (q / lam + rho0 + h)) that joins the upper half of a subsequence to the lower; the phases
+// exp(-2 pi i b (q + lam (rho0 + h)) / (lam P)), b = 1..P1-1 (the premultiplying phase of (presA) and the
+// modulation that moves the class to slot 0); D[n2][r''] = Tf_q[0] HT_q[n2][(rho0 + h + halves r'') mod P].
+// Behind the terms, with J = j + g h running over the residues and classes, TW[f][J] = exp(2 pi i
+// c1(f) (j + lam h) / M): the P1-point inverse transform over the slots leaves at f the output
+// c1(f) = f (lam / g)^-1 mod P1 and those P1 apart, and J is the index of the transform over c2 that
+// follows. LR[f][c2] = c1(f) + P1 c2.
+void build_lt(AxisTables& t, int64_t M, int64_t lam, int halves) {
+    const int64_t g = gcd_of(lam, M), P = M / g, lg = (lam / g) % P, P1 = P / halves, G = g * halves;
     int64_t inv = 0;
     for (int64_t x = 0; x < P; ++x)
         if ((x * lg) % P == 1 % P) { inv = x; break; }
-    const int64_t row = M + P - 1;
-    t.LT.assign(2 * (size_t)(lam * row + M), 0.0);
+    const int64_t row = g * P1 + P1 + halves - 2;
+    t.LT.assign(2 * (size_t)(lam * halves * row + M), 0.0);
     t.LR.assign((size_t)M, 0);
     for (int64_t q = 0; q < lam; ++q) {
         const int64_t k = q / g;
         const int64_t rho0 = (P - (k % P) * inv % P) % P;
-        for (int64_t b = 1; b < P; ++b)
-            put(t.LT, (size_t)(q * row + b - 1), -rational_cycles(b * (q + lam * rho0), lam * P), 1.0);
         const double fr = t.Tf[2 * (size_t)(q * M)], fi = t.Tf[2 * (size_t)(q * M) + 1];
-        for (int64_t n2 = 0; n2 < g; ++n2)
-            for (int64_t r = 0; r < P; ++r) {
-                const double* h = &t.HT[2 * (size_t)((q * P + (r + rho0) % P) * g + n2)];
-                double* d = &t.LT[2 * (size_t)(q * row + P - 1 + n2 * P + r)];
-                d[0] = fr * h[0] - fi * h[1];
-                d[1] = fr * h[1] + fi * h[0];
-            }
-    }
-    for (int64_t f = 0; f < P; ++f) {
-        const int64_t c1 = (f * inv) % P;
-        for (int64_t j = 0; j < g; ++j) {
-            put(t.LT, (size_t)(lam * row + f * g + j), rational_cycles(j * c1, M), 1.0);
-            t.LR[(size_t)(f * g + j)] = (int)(c1 + P * j);
+        for (int64_t h = 0; h < halves; ++h) {
+            const int64_t at = (q * halves + h) * row, Q = q + lam * (rho0 + h);
+            if (halves == 2) put(t.LT, (size_t)at, -rational_cycles(Q, 2 * lam), 1.0);
+            for (int64_t b = 1; b < P1; ++b)
+                put(t.LT, (size_t)(at + halves - 2 + b), -rational_cycles(b * Q, lam * P), 1.0);
+            for (int64_t n2 = 0; n2 < g; ++n2)
+                for (int64_t r = 0; r < P1; ++r) {
+                    const double* v = &t.HT[2 * (size_t)((q * P + (rho0 + h + halves * r) % P) * g + n2)];
+                    double* d = &t.LT[2 * (size_t)(at + P1 + halves - 2 + n2 * P1 + r)];
+                    d[0] = fr * v[0] - fi * v[1];
+                    d[1] = fr * v[1] + fi * v[0];
+                }
         }
+    }
+    for (int64_t f = 0; f < P1; ++f) {
+        const int64_t c1 = (f * inv) % P1;
+        for (int64_t J = 0; J < G; ++J) {
+            put(t.LT, (size_t)(lam * halves * row + f * G + J), rational_cycles(c1 * (J % g + lam * (J / g)), M), 1.0);
+            t.LR[(size_t)(f * G + J)] = (int)(c1 + P1 * J);
+        }
+    }
+}
+
+// Table of the lane-per-line E kernel: per term the phases TA_q[g b], b = 1..P-1, then HT_q[n2][r].
+void build_et(AxisTables& t, int64_t M, int64_t lam) {
+    const int64_t g = gcd_of(lam, M), P = M / g, row = M + P - 1;
+    t.ET.assign(2 * (size_t)(lam * row), 0.0);
+    for (int64_t q = 0; q < lam; ++q) {
+        double* d = &t.ET[2 * (size_t)(q * row)];
+        for (int64_t b = 1; b < P; ++b, d += 2) {
+            d[0] = t.TA[2 * (size_t)(q * M + g * b)];
+            d[1] = t.TA[2 * (size_t)(q * M + g * b) + 1];
+        }
+        for (int64_t n2 = 0; n2 < g; ++n2)
+            for (int64_t r = 0; r < P; ++r, d += 2) {
+                d[0] = t.HT[2 * (size_t)((q * P + r) * g + n2)];
+                d[1] = t.HT[2 * (size_t)((q * P + r) * g + n2) + 1];
+            }
     }
 }
 
@@ -290,8 +316,9 @@ AxisTables build_axis_tables(const AxisParams& p) {
         }
     }
     for (int64_t k = 0; k < M; ++k) put(t.tw, (size_t)k, -rational_cycles(k, M), 1.0);
-    if (p.want_ht || p.want_lt || p.fold) build_ht(t, M, lam);
-    if (p.want_lt) build_lt(t, M, lam);
+    if (p.want_ht || p.lt_halves || p.want_et || p.fold) build_ht(t, M, lam);
+    if (p.lt_halves) build_lt(t, M, lam, p.lt_halves);
+    if (p.want_et) build_et(t, M, lam);
     if (p.fold) build_ft(t, lam, *p.fold);
     if (p.want_ht) arrange_ht(t, M, lam);
     else t.HT.clear();
