@@ -1140,7 +1140,7 @@ const char* kernel_of(const fx_plan* p, const Op& o) {
     if (g.qc > 0) return o.kind == Kind::E ? "k_ER" : "k_EAR";
     const bool a = o.kind == Kind::A, ah = o.kind == Kind::AH;
     if ((a || ah) && g.reg_a && g.Qin * g.A * (int64_t)ax.P * g.S * 8 < (int64_t(1) << 31))
-        return ax.g <= 8 ? (a ? "k_ASR" : "k_AHR") : (a ? "k_ASK" : "k_AHK");
+        return ax.g <= 8 || (ax.g & (ax.g - 1)) != 0 ? (a ? "k_ASR" : "k_AHR") : (a ? "k_ASK" : "k_AHK");
     if (p2_applicable(o.kind, ax.M) && g.TS == p2_tile_lines(ax.M)) return o.kind == Kind::E ? "k_E2" : "k_EA2";
     if (ct_applicable(o.kind, ax.M) && g.TS == ct_tile_lines(ax.M)) return o.kind == Kind::E ? "k_Ect" : "k_EAct";
     switch (o.kind) {

@@ -239,7 +239,7 @@ int ehr_tile_lines(int g);
 hipError_t launch_pass_ehr(bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g, int accumulate,
                            hipStream_t st);
 // Structured accumulate (A) and its adjoint (AH) in registers: one thread per output group for
-// g <= 8, g / 8 lanes per group for g = 16, 32, 64.
+// g <= 10, 12 and 15, several lanes per group for g = 16, 32, 64.
 bool asr_applicable(int g, int max_g);
 hipError_t launch_pass_asr(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
                            int accumulate, void* rho, hipStream_t st);

@@ -18,6 +18,7 @@
 #include <set>
 
 #include "fx_internal.h"
+#include "butterflies.h"
 #include "device_common.h"
 
 namespace fx {
@@ -1804,6 +1805,12 @@ __device__ __forceinline__ AccGroup acc_group(unsigned gi, unsigned PS, unsigned
     return o;
 }
 
+// The G-point transform of an output group's residues, in registers.
+template <typename T, int G, bool INV> __device__ __forceinline__ void acc_dft(C<T>* v) {
+    if constexpr ((G & (G - 1)) == 0) RegDFT<T, G, INV>::run(v);
+    else bfly<T, G, INV>(v);
+}
+
 // Structured accumulate in registers: one thread per group (qo, a, n0, s). For the outputs
 // nbar = n0 + P c (c < g) every term reads the same input sample r(n0), and the twiddle (presf)
 // satisfies Tf_q[n0 + P c] = Tf_q[n0] exp(2 pi i q c / g), so with j = (q - qb) mod g
@@ -1846,7 +1853,7 @@ __global__ __launch_bounds__(kThreads) void k_ASR(const C<T>* __restrict__ in, C
 #pragma unroll
         for (int j = 0; j < G; ++j)
             if (i0 + j < g.qn) h[j] = cfma<T>(h[j], tf[(int64_t)(i0 + j) * M], src[(int64_t)(i0 + j) * step]);
-        RegDFT<T, G, true>::run(h);
+        acc_dft<T, G, true>(h);
 #pragma unroll
         for (int c = 0; c < G; ++c) {
             C<T> v = h[c];
@@ -2370,7 +2377,7 @@ __global__ __launch_bounds__(kThreads) void k_AHR(const C<T>* __restrict__ in, C
 #pragma unroll
             for (int c = 1; c < G; ++c) y[c] = cmul<T>(y[c], twg[((qbr * c) % G) * P]);  // exp(-2 pi i qb c / g)
         }
-        RegDFT<T, G, false>::run(y);
+        acc_dft<T, G, false>(y);
         for (int i0 = 0; i0 < g.qn; i0 += G) {
             C<T> t[G];
 #pragma unroll
@@ -2711,6 +2718,14 @@ hipError_t launch_ahr_T(const void* in, void* out, const AxisDev& ax, const Pass
         case 2: return launch_ahr<T, 2>(in, out, ax, g, accumulate, st);
         case 4: return launch_ahr<T, 4>(in, out, ax, g, accumulate, st);
         case 8: return launch_ahr<T, 8>(in, out, ax, g, accumulate, st);
+        case 3: return launch_ahr<T, 3>(in, out, ax, g, accumulate, st);
+        case 5: return launch_ahr<T, 5>(in, out, ax, g, accumulate, st);
+        case 6: return launch_ahr<T, 6>(in, out, ax, g, accumulate, st);
+        case 7: return launch_ahr<T, 7>(in, out, ax, g, accumulate, st);
+        case 9: return launch_ahr<T, 9>(in, out, ax, g, accumulate, st);
+        case 10: return launch_ahr<T, 10>(in, out, ax, g, accumulate, st);
+        case 12: return launch_ahr<T, 12>(in, out, ax, g, accumulate, st);
+        case 15: return launch_ahr<T, 15>(in, out, ax, g, accumulate, st);
         case 16:
             return ask_residues() == 4 ? launch_ahk<T, 4, 4>(in, out, ax, g, accumulate, st)
                                        : launch_ahk<T, 2, 8>(in, out, ax, g, accumulate, st);
@@ -2732,6 +2747,14 @@ hipError_t launch_asr_T(const void* in, void* out, const AxisDev& ax, const Pass
         case 2: return launch_asr<T, 2>(in, out, ax, g, accumulate, rho, st);
         case 4: return launch_asr<T, 4>(in, out, ax, g, accumulate, rho, st);
         case 8: return launch_asr<T, 8>(in, out, ax, g, accumulate, rho, st);
+        case 3: return launch_asr<T, 3>(in, out, ax, g, accumulate, rho, st);
+        case 5: return launch_asr<T, 5>(in, out, ax, g, accumulate, rho, st);
+        case 6: return launch_asr<T, 6>(in, out, ax, g, accumulate, rho, st);
+        case 7: return launch_asr<T, 7>(in, out, ax, g, accumulate, rho, st);
+        case 9: return launch_asr<T, 9>(in, out, ax, g, accumulate, rho, st);
+        case 10: return launch_asr<T, 10>(in, out, ax, g, accumulate, rho, st);
+        case 12: return launch_asr<T, 12>(in, out, ax, g, accumulate, rho, st);
+        case 15: return launch_asr<T, 15>(in, out, ax, g, accumulate, rho, st);
         case 16:
             return ask_residues() == 4 ? launch_ask<T, 4, 4>(in, out, ax, g, accumulate, rho, st)
                                        : launch_ask<T, 2>(in, out, ax, g, accumulate, rho, st);
@@ -3057,9 +3080,13 @@ hipError_t launch_eaw_T(const void* in, void* out, const AxisDev& ax, const Pass
 
 }  // namespace
 
-// g <= 8: one thread per group (k_ASR); g = 16, 32, 64: K = g / 8 lanes per group (k_ASK).
+// g <= 10, 12 and 15: one thread per group (k_ASR); g = 16, 32, 64: K = g / 8 lanes per group (k_ASK).
 bool asr_applicable(int g, int max_g) {
-    return (g == 1 || g == 2 || g == 4 || g == 8 || g == 16 || g == 32 || g == 64) && g <= max_g;
+    switch (g) {
+        case 1: case 2: case 3: case 4: case 5: case 6: case 7: case 8: case 9: case 10: case 12: case 15:
+        case 16: case 32: case 64: return g <= max_g;
+        default: return false;
+    }
 }
 
 hipError_t launch_pass_asr(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
