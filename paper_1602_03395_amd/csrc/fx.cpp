@@ -359,10 +359,19 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
         }
         return ops;
     }
+    // An axis with lam = 1 has the single term q = 0 with Tf_0 = 1 (free spectrum) and reads every sample at
+    // its own place (n'' = n), so its accumulate is the identity: the samples of E are the result, and
+    // the accumulate pass (a copy of the field: 92 us for 96 x 96 x 1080 in FP64) is left out. The first
+    // axis keeps its EA when no accumulate follows, since the last pass adds to the output and forms rho.
+    auto identity = [&](int ax) { return p->ax[ax].lam == 1 && !p->spectrum[ax]; };
     if (!adjoint) {
+        bool later = false;
+        for (int i = 1; i < k; ++i) later = later || !identity(p->act[i]);
         for (int i = k - 1; i >= 1; --i) do_E(p->act[i]);
-        do_EA(p->act[0]);
-        for (int i = 1; i < k; ++i) do_A(p->act[i]);
+        if (later && identity(p->act[0])) do_E(p->act[0]);
+        else do_EA(p->act[0]);
+        for (int i = 1; i < k; ++i)
+            if (!identity(p->act[i])) do_A(p->act[i]);
         // fuse the last two accumulate passes (axes u < v) into one 2-D structured accumulate
         const size_t n = ops.size();
         if (p->use_aa && n >= 2 && ops[n - 2].kind == Kind::A && ops[n - 1].kind == Kind::A) {
@@ -397,8 +406,10 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
             }
         }
     } else {
-        for (int i = k - 1; i >= 1; --i) do_AH(p->act[i]);
-        do_EAH(p->act[0]);
+        for (int i = k - 1; i >= 1; --i)
+            if (!identity(p->act[i])) do_AH(p->act[i]);
+        if (identity(p->act[0])) do_EH(p->act[0]);
+        else do_EAH(p->act[0]);
         for (int i = 1; i < k; ++i) do_EH(p->act[i]);
         // the adjoint of the fused accumulate: the first two AH passes (axes v > u), register form
         if (p->use_aa && ops.size() >= 2 && ops[0].kind == Kind::AH && ops[1].kind == Kind::AH &&

@@ -1,5 +1,5 @@
-"""Accumulates of axes whose g is no power of two in registers (k_ASR, k_AHR): against the FP64 oracle,
-forward, adjoint, partial term ranges."""
+"""Accumulates of axes whose g is no power of two in registers (k_ASR, k_AHR), and axes with lam = 1, whose
+accumulate is the identity and left out: against the FP64 oracle, forward, adjoint, partial term ranges."""
 
 import json
 import os
@@ -66,3 +66,28 @@ def test_register_accumulate_of_any_g(fx, g, dtype):
         print("accumulate g", g, shape, lam, dtype, flush=True)
         d = check(fx, shape, lam, dtype, 9000 + g)
         assert any(p["kernel"] == "k_AHR" and p["M"] == 4 * g for p in d["adjoint_passes"]), d
+
+
+IDENTITY = [((24, 20), (1, 4)), ((24, 20), (4, 1)), ((24, 20), (1, 1)), ((40,), (1,)), ((12, 10, 16), (1, 3, 1)),
+            ((12, 10, 16), (2, 1, 1)), ((12, 10, 16), (1, 1, 4)), ((12, 10, 16), (8, 8, 1)), ((1, 30), (3, 1))]
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("case", range(len(IDENTITY)))
+def test_unmagnified_axes(fx, case, dtype):
+    shape, lam = IDENTITY[case]
+    print("lam = 1", shape, lam, dtype, flush=True)
+    d = check(fx, shape, lam, dtype, 9100 + case)
+    for p in d["passes"] + d["adjoint_passes"]:
+        assert not (p["kind"] in ("A", "AH") and p["lam"] == 1), d
+
+
+def test_unmagnified_axis_with_a_spectrum_keeps_its_accumulate(fx):
+    # a tabulated spectrum may give the term q = 0 a phase, which the accumulate carries
+    shape, lam, dx, t = (18, 20), (3, 1), (1.0, 0.8), 5.0
+    f = workloads.random_field(shape, 9200)
+    spec = [0.3 + t * 0.5 * fx.fine_wavenumbers(m, l, d) ** 2 for m, l, d in zip(shape, lam, dx)]
+    out, _ = fx.expand(torch.from_numpy(f).cuda(), dx, 1.0, t, lam, spectrum=spec)
+    torch.cuda.synchronize()
+    ref = oracle.expand(f, dx, 1.0, t, lam) * np.exp(-0.6j)
+    assert rel(out.cpu().numpy(), ref) <= 1e-12
