@@ -24,12 +24,14 @@ _PLAN_LOCK = threading.Lock()
 _PLAN_CACHE_MAX = 32
 
 
-def _stream_ptr() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream_ptr() -> int:
+    # the current stream of the current device, without the Stream object: 3 of the 14 us that a
+    # two-launch expansion takes on the host went into building one per call
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-def _ptr(t: Optional[torch.Tensor]) -> Optional[ctypes.c_void_p]:
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _check_field(x: torch.Tensor, name: str):
