@@ -52,6 +52,32 @@ inline double beta_cycles(DD beta, int64_t I) {
     return reduce_cycles(reduce_cycles(p) + e + beta.lo * x);
 }
 
+// exp(-2 pi i k / N), k < N, from one table: the premultiplying phases and the twiddles of HT are all among
+// them. Above 2^22 entries they are computed one by one.
+class Roots {
+public:
+    explicit Roots(int64_t N) : N_(N) {
+        if (N > (int64_t(1) << 22)) return;
+        tab_.resize(2 * (size_t)N);
+        for (int64_t k = 0; k < N; ++k) value(k, &tab_[2 * (size_t)k]);
+    }
+    int64_t size() const { return N_; }
+    void get(int64_t k, double* z) const {  // 0 <= k < N
+        if (tab_.empty()) return value(k, z);
+        z[0] = tab_[2 * (size_t)k];
+        z[1] = tab_[2 * (size_t)k + 1];
+    }
+
+private:
+    void value(int64_t k, double* z) const {
+        const double ang = -kTwoPi * rational_cycles(k, N_);
+        z[0] = std::cos(ang);
+        z[1] = std::sin(ang);
+    }
+    int64_t N_;
+    std::vector<double> tab_;
+};
+
 inline void put(std::vector<double>& v, size_t i, double cycles, double amp) {
     const double ang = kTwoPi * reduce_cycles(cycles);
     v[2 * i] = amp * std::cos(ang);
@@ -72,7 +98,7 @@ int64_t gcd_of(int64_t g, int64_t b) {
 // where the n2 part of (presA), TA'[n2] = exp(-2 pi i q n2 / (lam M)), and the 1/M of the inverse
 // are folded in as well. Layout [q][r][n2] (the g lanes of a line read consecutive values, and the
 // P g = M values of one q are contiguous), FP64 complex.
-void build_ht(AxisTables& t, int64_t M, int64_t lam) {
+void build_ht(AxisTables& t, int64_t M, int64_t lam, const Roots& roots) {
     const int64_t g = gcd_of(lam, M);
     const int64_t P = M / g;
     const int64_t N = lam * M;
@@ -98,8 +124,9 @@ void build_ht(AxisTables& t, int64_t M, int64_t lam) {
                     continue;
                 }
                 // exp(-2 pi i (n2 r lam + q n2) / (lam M)) / M
-                const double ang = -kTwoPi * rational_cycles(n2 * r * lam + q * n2, N);
-                const double er = std::cos(ang) / (double)M, ei = std::sin(ang) / (double)M;
+                double z[2];
+                roots.get((n2 * (r * lam + q)) % N, z);
+                const double er = z[0] / (double)M, ei = z[1] / (double)M;
                 t.HT[i] = sr * er - si * ei;
                 t.HT[i + 1] = sr * ei + si * er;
             }
@@ -294,12 +321,13 @@ AxisTables build_axis_tables(const AxisParams& p) {
 
     const double inv2pi = 1.0 / kTwoPi;
     const int64_t l0 = N / 2;  // table index of the fine wave number 0
+    const Roots roots(N);
     for (int64_t q = 0; q < lam; ++q) {
         const double phq = p.phase ? p.phase[l0 + q] * inv2pi : 0.0;
         for (int64_t n = 0; n < M; ++n) {
             const size_t i = (size_t)(q * M + n);
-            // TA: -(q n)/(lam M)
-            put(t.TA, i, -rational_cycles(q * n, N), 1.0);
+            // TA: -(q n)/(lam M); q n < lam M
+            roots.get(q * n, &t.TA[2 * i]);
             // TB: coarse wave number of eq. (kj) with the odd-M umklapp.
             int64_t lt = (2 * n < M) ? n : n - M;
             if ((M % 2 == 1) && (2 * n == M - 1) && (2 * q >= lam)) lt -= M;
@@ -316,7 +344,7 @@ AxisTables build_axis_tables(const AxisParams& p) {
         }
     }
     for (int64_t k = 0; k < M; ++k) put(t.tw, (size_t)k, -rational_cycles(k, M), 1.0);
-    if (p.want_ht || p.lt_halves || p.want_et || p.fold) build_ht(t, M, lam);
+    if (p.want_ht || p.lt_halves || p.want_et || p.fold) build_ht(t, M, lam, roots);
     if (p.lt_halves) build_lt(t, M, lam, p.lt_halves);
     if (p.want_et) build_et(t, M, lam);
     if (p.fold) build_ft(t, lam, *p.fold);
