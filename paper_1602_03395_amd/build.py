@@ -17,7 +17,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfx.so")
-SOURCES = ["fx.cpp", "tables.cpp", "batch.cpp", "kernels.hip", "kernels_p2.hip", "kernels_ct.hip", "kernels_cfp.hip", "kernels_fold.hip", "kernels_lane.hip", "pair.hip", "farfield.hip", "brute.hip", "noalloc.hip"]
+SOURCES = ["fx.cpp", "tables.cpp", "batch.cpp", "kernels.hip", "kernels_p2.hip", "kernels_ct.hip", "kernels_cfp.hip", "kernels_fold.hip", "kernels_lane.hip", "kernels_wave.hip", "pair.hip", "farfield.hip", "brute.hip", "noalloc.hip"]
 
 # Per-source flags. kernels_fold.hip: its kernels switch between many butterflies inside the loop over the
 # terms; hoisting the FP64 constants of all of them out of that loop costs hundreds of scalar-register spills.

@@ -201,6 +201,19 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
             g.fqpw = (int)std::min<int64_t>(g.qn, std::max<int64_t>(8, (w + 7) / 8 * 8));
             return g;
         }
+        // Rows in registers, for many subsequences, rounds of 16 terms that are mostly full, and 16 rows per
+        // CU at least. Against the folded E, with the accumulate, FP32 / FP64: g = 8, 40 terms, 2080 rows
+        // 33 -> 31 / 47 -> 38 us, 8400 rows 87 -> 46 / 140 -> 94, 320 rows 15 -> 28 / 19 -> 31; 24 terms, 4200 rows
+        // 47 -> 37 / 74 -> 61; 8 terms (half the rows idle), 4200 rows 44 -> 37 / 71 -> 77; g = 16, 16 terms, FP32,
+        // 4192 rows 87 -> 55. Few subsequences gain nothing: g = 1, 5 terms, 4200 rows 24 -> 25 us; g = 2, 6 terms 23 -> 23.
+        const int64_t rows = g.Qin * g.A * g.qn;
+        g.ew = kind == Kind::E && p->use_cfp && p->use_ew && g.S == 1 && p->ax[ax].ET != nullptr &&
+               ew_applicable(p->dbl, p->ax[ax].M, p->ax[ax].g) && p->ax[ax].g >= 8 && ew_fill(g.qn) >= 0.6 &&
+               rows >= 16 * (int64_t)num_cus() && rows < (int64_t(1) << 30);
+        if (g.ew) {
+            g.fqpw = ew_terms(g.Qin * g.A, g.qn, num_cus());
+            return g;
+        }
         g.eaw = kind == Kind::EA && p->use_cfp && p->use_eaw && p->ax[ax].HTx != nullptr &&
                 eaw_applicable(p->dbl, p->ax[ax].M, p->ax[ax].g, qn[ax]);
         g.erw = kind == Kind::E && p->use_cfp && p->use_erw > 0 && p->ax[ax].HT != nullptr && g.S == 1 &&
@@ -318,6 +331,9 @@ std::vector<Op> build_ops(const fx_plan* p, const int qb[3], const int qn[3], in
         const double bytes = (double)vol() * csize(p) * ((double)p->ax[ax].P / p->ax[ax].M * qn[ax] + 1.5);
         if (vol() / p->ax[ax].M * p->ax[ax].P * (double)qn[ax] >= (double)(kIndexLimit / 4)) return false;
         const PassGeom gs = geom(Kind::E, ax, slices);
+        // E with the rows in registers and an accumulate: 33000 rows of g = 8, 24 terms, FP32 280 -> 123 us; 40960 rows, 40
+        // terms, FP32 300 -> 127, FP64 572 -> 308
+        if (gs.ew) return true;
         return gs.fold && ge.fcycles > gs.fcycles + (bytes / 5e6 + 4.0) * (2400.0 / 1.5);
     };
     auto do_EA = [&](int ax) {
@@ -740,6 +756,8 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
             if (eal_applicable(p->dbl, ad.M, ad.g)) ap.lt_halves = eal_halves(p->dbl, ad.M, ad.g);
             ap.want_et = el_applicable(p->dbl, ad.M, ad.g);
         }
+        // rows in registers: for the axis whose lines are contiguous
+        if (pa == 2 && ap.lam * ap.M <= (int64_t(1) << 22) && ad.g >= 8 && ew_applicable(p->dbl, ad.M, ad.g)) ap.want_et = true;
         if (!reg && !(ad.M == 1 && ad.lam == 1) && ap.lam * ap.M <= (int64_t(1) << 23) &&
             ap.lam * ap.M * (int64_t)ad.g <= (int64_t(1) << 26) && make_fold_plan(p->foldp[pa], ad.M, ad.g)) {
             ad.fold = &p->foldp[pa];
@@ -841,6 +859,7 @@ fx_status create_plan(const fx_problem* prob, const double* const* phase, fx_pla
     if (const char* e = std::getenv("FX_ERW")) p->use_erw = std::atoi(e);
     if (std::getenv("FX_NO_EH2")) p->use_eh2 = false;
     if (const char* e = std::getenv("FX_EAL")) p->use_eal = (e[0] != '0');
+    if (const char* e = std::getenv("FX_EW")) p->use_ew = (e[0] != '0');
     if (const char* e = std::getenv("FX_FOLD")) p->use_fold = (e[0] != '0');
     if (const char* e = std::getenv("FX_ASR_MAXG")) p->asr_max_g = std::max(1, std::atoi(e));
     p->cfp_blocks = 2 * num_cus();
@@ -1143,6 +1162,7 @@ const char* kernel_of(const fx_plan* p, const Op& o) {
     if (o.kind == Kind::EH && g.erg) return "k_EHG";
     if (g.eal) return o.kind == Kind::EA ? "k_EAL" : "k_EAHL";
     if (g.el) return "k_EL";
+    if (g.ew) return "k_EW";
     if (o.kind == Kind::EA && g.eaw) return "k_EAW";
     if (o.kind == Kind::EA && g.eas) return "k_EAS";
     if (g.qc > 0 && o.kind == Kind::EH) return "k_EHR";
@@ -1196,7 +1216,7 @@ fx_status fx_plan_describe(const fx_plan* p, char* buf, size_t len) {
                       "\"A\":%lld,\"S\":%lld,\"TS\":%d,\"reg\":%d",
                       i ? "," : "", names[(int)o.kind], o.axis - (3 - p->ndim), a.M, a.P, a.lam, o.g.qn,
                       (long long)o.g.Qin, (long long)o.g.A, (long long)o.g.S, o.g.TS,
-                      (o.g.qc > 0 || o.g.reg_a || o.g.eas || o.g.eaw || o.g.eal || o.g.el) ? 1 : 0);
+                      (o.g.qc > 0 || o.g.reg_a || o.g.eas || o.g.eaw || o.g.eal || o.g.el || o.g.ew) ? 1 : 0);
         s += tmp;
         s += std::string(",\"kernel\":\"") + kernel_of(p, o) + "\"";
         if (o.g.eas || o.g.eaw || o.g.eal || (o.g.erg && o.kind == Kind::EA)) s += ",\"eas\":1";

@@ -65,7 +65,7 @@ struct AxisDev {
                                // P <= min(g, 8) row n2 turned by bitrev(n2 mod P), else HTx reordered
     const void* LT = nullptr;  // table of the lane-per-line EA (or null)
     const int* LR = nullptr;   // its output rows
-    const void* ET = nullptr;  // table of the lane-per-line E (or null)
+    const void* ET = nullptr;  // table of the lane-per-line E and the rows-in-registers E (or null)
     const void* FT = nullptr;  // table of the folded line kernels (or null)
     const FoldPlan* fold = nullptr;   // plan of those kernels (or null): host copy
     const FoldPlan* foldd = nullptr;  // and device copy
@@ -100,6 +100,7 @@ struct PassGeom {
     bool eh2 = false;    // EH pass: compile-time power-of-two kernel, one output line per workgroup
     bool eal = false;    // EA or EAH pass: one line per lane, tiles of 64 lines over all slices
     bool el = false;     // E pass: one line per lane, fqpw terms per workgroup
+    bool ew = false;     // E pass of contiguous lines, P = 256: the rows of a wave in registers, fqpw terms per workgroup
     // E, EA or EH pass by the folded line kernels: 2^flts lines and fqr terms per step, fqpw terms per
     // workgroup (E), fgs groups of subsequences summed side by side, input read from global memory
     // instead of an LDS copy (fdirect); LDS strides of a slot, a row and a raw line. For contiguous
@@ -176,7 +177,7 @@ struct AxisParams {
     const double* phase = nullptr;
     bool want_ht = false;  // also build the chirp-folded table HT in its register-kernel layouts
     int lt_halves = 0;     // > 0: also build the table of the lane-per-line EA, this many classes of slots
-    bool want_et = false;  // also build the table of the lane-per-line E
+    bool want_et = false;  // also build the table of the lane-per-line E and of the rows-in-registers E
     const FoldPlan* fold = nullptr;  // also build the rows of the folded line kernels for this plan
 };
 AxisTables build_axis_tables(const AxisParams& p);
@@ -260,6 +261,12 @@ int lane_tile_lines();
 hipError_t launch_pass_eal(Kind kind, bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g,
                            int accumulate, void* rho, hipStream_t st);
 hipError_t launch_pass_el(bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g, hipStream_t st);
+
+// E of contiguous lines for P = 256, the rows of a wave in registers (kernels_wave.hip).
+bool ew_applicable(bool dbl, int M, int g);
+double ew_fill(int qn);
+int ew_terms(int64_t lines, int qn, int cus);
+hipError_t launch_pass_ew(bool dbl, const void* in, void* out, const AxisDev& ax, const PassGeom& g, hipStream_t st);
 
 void set_error(const std::string& msg);
 

@@ -737,6 +737,7 @@ hipError_t launch_pass(Kind kind, bool dbl, const void* in, void* out, const Axi
                        int accumulate, void* rho, hipStream_t st) {
     if (g.eal) return launch_pass_eal(kind, dbl, in, out, ax, g, accumulate, rho, st);
     if (g.el) return launch_pass_el(dbl, in, out, ax, g, st);
+    if (g.ew) return launch_pass_ew(dbl, in, out, ax, g, st);
     // tile kernels index their tiles with 32-bit integers (the count includes the padding of the
     // XCD-aware order of the register E kernel)
     if (((g.Qin * g.ntiles + 7) / 8) * 8 * g.qn >= (int64_t(1) << 31)) return hipErrorInvalidValue;

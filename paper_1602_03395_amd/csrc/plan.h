@@ -76,6 +76,7 @@ struct fx_plan {
     mutable std::mutex fold_mu;
     mutable std::vector<FoldMemo> fold_memo;
     bool use_eal = true;           // lane-per-line EA, EAH and E where there are enough lines (FX_EAL=0 disables)
+    bool use_ew = true;            // E with the rows of a wave in registers (FX_EW=0 disables)
     bool use_fold = true;          // folded line kernels where no register kernel applies (FX_FOLD=0 disables)
     bool use_eh2 = true;           // compile-time power-of-two EH kernel (FX_NO_EH2 disables)
     int use_aa = 1;                // fuse the last two accumulate passes: 0 never (FX_AA=0), 1 in

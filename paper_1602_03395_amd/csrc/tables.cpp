@@ -276,7 +276,7 @@ void build_lt(AxisTables& t, int64_t M, int64_t lam, int halves) {
     }
 }
 
-// Table of the lane-per-line E kernel: per term the phases TA_q[g b], b = 1..P-1, then HT_q[n2][r].
+// Table of the lane-per-line E and of the rows-in-registers E: per term the phases TA_q[g b], b = 1..P-1, then HT_q[n2][r].
 void build_et(AxisTables& t, int64_t M, int64_t lam) {
     const int64_t g = gcd_of(lam, M), P = M / g, row = M + P - 1;
     t.ET.assign(2 * (size_t)(lam * row), 0.0);
