@@ -10,9 +10,10 @@
 // What bounds it: latency of the exchange and of the table rows (3 waves per SIMD in FP32, 1 in FP64) for a few
 // thousand rows, VALU issue above: 2048 points, g = 8, 40 terms, E + A, FP32, 2560 / 10240 / 40960 rows
 // 34 / 104 / 300 -> 32 / 49 / 127 us (the last against the fused folded EA), FP64 54 / 176 / 572 -> 40 / 101 /
-// 308 us. Rows straight from global memory (no line in LDS) took 95 us for 20480 rows in FP32: each of the 8
-// passes over a line reads all its memory lines again. The same form for P = 128 and 512 was slower than the folded
-// kernels (FP32 P = 512: 42 -> 40 us for 5120 rows, 27 -> 32 for 1280; P = 128, 8192 rows of g = 8: 39 -> 39 us).
+// 308 us. Rows straight from global memory (no line in LDS) took 135 us for 20480 rows in FP32: each of the 8 passes
+// over a line reads all its memory lines again. The same form for P = 512 in FP32 (one wave per SIMD) gained from
+// 10240 rows of g = 8 on only (178 -> 142 us; g = 4, 1280 rows 27 -> 32, 20480 rows 165 -> 194), for P = 128 in FP32 not
+// at all (g = 8, 2048 rows 16 -> 20 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
